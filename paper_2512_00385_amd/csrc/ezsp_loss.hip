@@ -10,23 +10,39 @@
 // row q does not list p.  That slot's caller-supplied random word draws the
 // pair.  With rho < 1 the sample keeps m = min(n_intra,
 // floor(rho * n_inter / (1 - rho))) intra pairs: those whose 64-bit key
-// (word, slot) is among the m smallest, found exactly by an 8-pass MSB radix
-// select over the keys (keys are distinct, so the m-th smallest is a sharp
-// threshold).  Every inter pair is kept.
+// (word, slot) is among the m smallest (keys are distinct, so the m-th
+// smallest is a sharp threshold).  Every inter pair is kept.
 //
 // Distances, affinities, loss terms and gradient contributions are fp32; the
 // loss is summed in fp64.  -log a is d / tau and -log(1 - a) is
 // -log(-expm1(-d / tau)); the gradient of |e_p - e_q| at e_p = e_q is 0.
 //
-// Layout: a group of G lanes (the power of two >= max(D, k), at most 64) owns
-// one row p of the table, lane i holding embedding dimensions i, i + G, ...;
-// every e_q gather is then one contiguous segment.  The row accumulates the
-// gradient on its own side of every sampled pair it lists in registers; the
-// other end q gets its side from its own row when q lists p too (a mutual
-// pair), and by atomics from the owner slot otherwise.  A slot's 16-bit
-// status carries the pair type, whether it owns the pair, whether the pair is
-// mutual, and where row q lists p, so a mirror slot can read the owner's
-// random word.
+// Layout: a group of G lanes owns one row p of the table, lane i holding
+// V consecutive dimensions (a 16-byte vector where rows allow it) of every
+// chunk of G * V.  Lane t also classifies slot t of the row and, once the
+// group has its distance, evaluates its affinity and loss term; so the
+// transcendental functions run once a slot and not once a lane.
+//
+// Passes (driving tile of 3M points, k = 8, D = 32, rho = 0.3):
+//   k_le_pairs   classification, distances, affinities, the inter pairs'
+//                loss and gradient, and a histogram of the intra pairs' words
+//   k_le_pick    the sample's size, and the histogram bin its threshold is in
+//   k_le_sample  the intra pairs below that bin: loss and gradient; those in
+//                it are listed
+//   k_le_select  the threshold among the listed keys
+//   k_le_listed  the listed pairs up to the threshold
+// The embedding rows and the neighbours' table rows are gathered once; a
+// small sample's rows are gathered again.  When the sample is a large part of
+// the slots, or the threshold's bin overflows the list (equal words), the
+// host runs the radix select over all slots and a row-wise pass instead
+// (k_le_hist, k_le_digit, k_le_dense).
+//
+// The row accumulates the gradient on its own side of every sampled pair it
+// lists in registers; the other end q gets its side from its own row when q
+// lists p too (a mutual pair), and by atomics from the owner slot otherwise.
+// A slot's 16-bit status carries the pair type, whether it owns the pair,
+// whether the pair is mutual, and where row q lists p, so a mirror slot can
+// read the owner's random word.
 #include "ezsp_internal.h"
 
 namespace ezsp {
@@ -44,106 +60,548 @@ enum : uint16_t {
 };
 
 constexpr int kLeNT = 256;
-constexpr int kLeGrid = 2048;  // grid-stride kernels: one atomic per block
+constexpr int kLeGrid = 2048;     // grid-stride kernels: blocks at most
+constexpr int kLeBitsMin = 8;     // word bits of the first histogram
+constexpr int kLeBitsMax = 12;
+constexpr int kLeCopies = 4;      // copies of it (atomics on one address)
+constexpr int kLeList = 16384;    // listed keys the threshold is found among
+constexpr int kLeTile = 2048;     // slots per step of k_le_sample
+constexpr int kLeStage = 1024 + kLeTile;  // keys a block stages for the list
+
+// Word bits of the first histogram: about half the list's capacity of intra
+// pairs a bin, if every other slot owned one.
+int hist_bits(int64_t ns) {
+  int b = kLeBitsMin;
+  while (b < kLeBitsMax && (ns >> (b + 1)) > kLeList / 2) ++b;
+  return b;
+}
 
 template <class T>
 __device__ __forceinline__ T block_sum(T v, T *sh) {
   v = wave_sum(v);
   const int wid = threadIdx.x / kWave;
+  __syncthreads();
   if ((threadIdx.x & (kWave - 1)) == 0) sh[wid] = v;
   __syncthreads();
   T s = 0;
   if (threadIdx.x == 0)
-    for (int w = 0; w < kLeNT / kWave; ++w) s += sh[w];
+    for (int w = 0; w < (int)blockDim.x / kWave; ++w) s += sh[w];
   return s;  // valid in thread 0
 }
 
-// Slot status and the pair counts.
-// Position of p in row r (k entries), or -1; rows of 4k ids are read as
-// int4 (the table is 16-byte aligned then).
-template <bool VEC4>
-__device__ __forceinline__ int32_t find_in_row(const int32_t *r, int32_t k,
-                                               int32_t p) {
-  if (VEC4) {
+// First position of p in row r (k entries), or -1.  Rows of 4k (2k) ids at a
+// 16-byte (8-byte) aligned table are read as vectors.
+template <int VN>
+__device__ __forceinline__ int32_t find_in_row(const int32_t *__restrict__ r,
+                                               int32_t k, int32_t p) {
+  int32_t at = -1;
+  if (VN == 4) {
     const int4 *r4 = reinterpret_cast<const int4 *>(r);
-    for (int32_t t = 0; t < k / 4; ++t) {
+#pragma unroll 4
+    for (int32_t t = k / 4 - 1; t >= 0; --t) {
       const int4 x = r4[t];
-      if (x.x == p) return 4 * t;
-      if (x.y == p) return 4 * t + 1;
-      if (x.z == p) return 4 * t + 2;
-      if (x.w == p) return 4 * t + 3;
+      at = x.w == p ? 4 * t + 3 : at;
+      at = x.z == p ? 4 * t + 2 : at;
+      at = x.y == p ? 4 * t + 1 : at;
+      at = x.x == p ? 4 * t : at;
     }
-    return -1;
+  } else if (VN == 2) {
+    const int2 *r2 = reinterpret_cast<const int2 *>(r);
+#pragma unroll 8
+    for (int32_t t = k / 2 - 1; t >= 0; --t) {
+      const int2 x = r2[t];
+      at = x.y == p ? 2 * t + 1 : at;
+      at = x.x == p ? 2 * t : at;
+    }
+  } else {
+#pragma unroll 8
+    for (int32_t t = k - 1; t >= 0; --t) at = r[t] == p ? t : at;
   }
-  for (int32_t t = 0; t < k; ++t)
-    if (r[t] == p) return t;
-  return -1;
+  return at;
 }
 
-template <bool VEC4>
-__global__ __launch_bounds__(kLeNT) void k_le_classify(
-    const int32_t *__restrict__ nbr, int32_t n, int32_t k,
-    const int32_t *__restrict__ cls, uint16_t *__restrict__ status,
-    Ctl *ctl) {
-  __shared__ unsigned long long sh[kLeNT / kWave];
-  const int64_t ns = (int64_t)n * k;
-  unsigned long long edges = 0, intra = 0;
-  for (int64_t s = blockIdx.x * (int64_t)kLeNT + threadIdx.x; s < ns;
-       s += (int64_t)gridDim.x * kLeNT) {
-    const int32_t p = (int32_t)(s / k);
-    const int32_t j = (int32_t)(s - (int64_t)p * k);
-    const int32_t q = nbr[s];
-    uint16_t v = kSlotNone;
-    if (q < -1 || q >= n) {
-      raise_err(ctl, kErrBadIndex);
-    } else if (q >= 0 && q != p) {
-      bool first = true;  // no earlier slot of row p lists q
-      const int32_t *row = nbr + (int64_t)p * k;
-      for (int32_t t = 0; t < j && first; ++t) first = row[t] != q;
-      if (first) {
-        const int32_t jq = find_in_row<VEC4>(nbr + (int64_t)q * k, k, p);
-        const bool mutual = jq >= 0;
-        const bool owner = p < q || !mutual;
-        v = (cls[p] == cls[q]) ? kSlotIntra : kSlotInter;
-        if (owner) v |= kSlotOwner;
-        if (mutual) v |= kSlotMutual | (uint16_t)(jq << 8);
-        if (owner) {
-          edges += 1;
-          intra += ((v & 3) == kSlotIntra);
-        }
+// A lane's part of an embedding row.
+template <int G, int V, int NV>
+struct RowPart {
+  float v[NV][V];
+  __device__ __forceinline__ void load(const float *__restrict__ emb,
+                                       int64_t p, int32_t d, int lane,
+                                       bool live) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      const int i = (c * G + lane) * V;
+      if (V == 4) {
+        const float4 x =
+            live && i < d ? *reinterpret_cast<const float4 *>(emb + p * d + i)
+                          : make_float4(0.f, 0.f, 0.f, 0.f);
+        v[c][0] = x.x;
+        v[c][1 % V] = x.y;
+        v[c][2 % V] = x.z;
+        v[c][3 % V] = x.w;
+      } else {
+        v[c][0] = live && i < d ? emb[p * d + i] : 0.0f;
       }
     }
-    status[s] = v;
   }
-  const unsigned long long e = block_sum(edges, sh);
+};
+
+// Sum over the G lanes of a group, the same in every lane: DPP within 16
+// lanes (quad permutes, half-row and row mirrors), shuffles beyond.
+template <int G>
+__device__ __forceinline__ float group_sum(float x) {
+#define EZSP_DPP(ctrl)                                                      \
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), ctrl, 0xf, \
+                                               0xf, true))
+  if (G >= 2) EZSP_DPP(0xb1);   // quad_perm(1, 0, 3, 2)
+  if (G >= 4) EZSP_DPP(0x4e);   // quad_perm(2, 3, 0, 1)
+  if (G >= 8) EZSP_DPP(0x141);  // row_half_mirror
+  if (G >= 16) EZSP_DPP(0x140);  // row_mirror
+#undef EZSP_DPP
+  if (G >= 32) x += __shfl_xor(x, 16, kWave);
+  if (G >= 64) x += __shfl_xor(x, 32, kWave);
+  return x;
+}
+
+template <int G, int V, int NV>
+__device__ __forceinline__ float squared(const RowPart<G, V, NV> &a,
+                                         const RowPart<G, V, NV> &b) {
+  float part = 0.0f;
+#pragma unroll
+  for (int c = 0; c < NV; ++c)
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const float df = a.v[c][v] - b.v[c][v];
+      part += df * df;
+    }
+  return group_sum<G>(part);
+}
+
+// grad row p += x
+template <int G, int V, int NV>
+__device__ __forceinline__ void add_row(float *grad, int64_t p, int32_t d,
+                                        int lane,
+                                        const RowPart<G, V, NV> &x) {
+#pragma unroll
+  for (int c = 0; c < NV; ++c)
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const int i = (c * G + lane) * V + v;
+      if (i < d) unsafeAtomicAdd(grad + p * d + i, x.v[c][v]);
+    }
+}
+
+// d loss / d dist / dist of a pair at distance dist, x = dist / tau
+__device__ __forceinline__ float pair_coef(bool intra, float dist, float x,
+                                           float inv_tau) {
+  if (!(dist > 0.0f)) return 0.0f;
+  return intra ? inv_tau / dist : -inv_tau / (expm1f(x) * dist);
+}
+
+__device__ __forceinline__ float pair_term(bool intra, float x) {
+  return intra ? x : -logf(-expm1f(-x));
+}
+
+// The gradient arrays and histograms start at zero.
+__global__ __launch_bounds__(kLeNT) void k_le_clear(float *grad,
+                                                    int64_t count,
+                                                    uint32_t *hist,
+                                                    int32_t nh) {
+  const int64_t t = blockIdx.x * (int64_t)kLeNT + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * kLeNT;
+  for (int64_t i = t; i < nh; i += step) hist[i] = 0;
+  if (!grad) return;
+  int64_t done = 0;
+  if ((reinterpret_cast<uintptr_t>(grad) & 15) == 0) {
+    float4 *g4 = reinterpret_cast<float4 *>(grad);
+    for (int64_t i = t; i < count / 4; i += step)
+      g4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    done = count / 4 * 4;
+  }
+  for (int64_t i = done + t; i < count; i += step) grad[i] = 0.0f;
+}
+
+// Everything that needs every slot: see the head of the file.  Bound by its
+// gathers: a random-order cloud of 3M points at k = 8, D = 32 fetches an
+// embedding row, a table row and a class per slot.
+template <int G, int V, int NV, int VN>
+__global__ __launch_bounds__(kLeNT) void k_le_pairs(
+    const float *__restrict__ emb, int32_t n, int32_t d,
+    const int32_t *__restrict__ nbr, int32_t k,
+    const int32_t *__restrict__ cls, const uint32_t *__restrict__ word,
+    float tau, bool take_all, int bits, uint16_t *__restrict__ status,
+    float *__restrict__ affinity, float *__restrict__ grad,
+    uint8_t *__restrict__ sampled, uint32_t *__restrict__ hist,
+    unsigned long long *__restrict__ part_edges,
+    unsigned long long *__restrict__ part_intra,
+    double *__restrict__ part_loss, Ctl *ctl) {
+  constexpr int kRows = kLeNT / G;  // rows per block and step
+  constexpr int U = NV == 1 ? 4 : (NV == 2 ? 2 : 1);  // gathers in flight
+  __shared__ uint32_t h[1 << kLeBitsMax];
+  __shared__ double shd[kLeNT / kWave];
+  __shared__ unsigned long long shu[kLeNT / kWave];
+  const int lane = threadIdx.x & (G - 1);
+  const int shift0 = (int)(threadIdx.x & (kWave - 1) & ~(G - 1));
+  const uint64_t gmask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1);
+  const float inv_tau = 1.0f / tau;
+  for (int i = threadIdx.x; i < (1 << bits); i += kLeNT) h[i] = 0;
   __syncthreads();
-  const unsigned long long i = block_sum(intra, sh);
+  unsigned long long edges = 0, intra = 0;
+  double lsum = 0.0;
+  bool finite = true, inside = true;
+  for (int64_t p = (int64_t)blockIdx.x * kRows + threadIdx.x / G; p < n;
+       p += (int64_t)gridDim.x * kRows) {
+    const int32_t *row = nbr + p * k;
+    RowPart<G, V, NV> ep, acc;
+    ep.load(emb, p, d, lane, true);
+#pragma unroll
+    for (int c = 0; c < NV; ++c)
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        finite = finite && isfinite(ep.v[c][v]);
+        acc.v[c][v] = 0.0f;
+      }
+    const int32_t cp = cls[p];
+    bool any = false;
+    for (int32_t r0 = 0; r0 < k; r0 += G) {
+      // lane t classifies slot r0 + t
+      const int32_t j = r0 + lane;
+      const bool slot = j < k;
+      int32_t q = slot ? row[j] : -1;
+      if (q < -1 || q >= n) {
+        inside = false;
+        q = -1;
+      }
+      uint32_t st = kSlotNone;
+      if (q >= 0 && q != p) {
+        const int32_t jq = find_in_row<VN>(nbr + (int64_t)q * k, k, (int32_t)p);
+        const int32_t jp = find_in_row<VN>(row, k, q);
+        if (jp == j) {  // no earlier slot of row p lists q
+          st = cls[q] == cp ? kSlotIntra : kSlotInter;
+          if (p < q || jq < 0) st |= kSlotOwner;
+          if (jq >= 0) st |= kSlotMutual | (uint32_t)(jq << 8);
+        }
+      }
+      const bool owner = (st & kSlotOwner) != 0;
+      const bool same = (st & 3) == kSlotIntra;
+      const bool take = (st & 3) == kSlotInter || (take_all && same);
+      edges += owner;
+      intra += owner && same;
+      if (!take_all && owner && same)
+        atomicAdd(&h[word[p * k + j] >> (32 - bits)], 1u);
+      const uint64_t takes = (__ballot(take) >> shift0) & gmask;
+      const uint64_t ones = (__ballot(!(st & kSlotMutual)) >> shift0) & gmask;
+      const uint64_t sames = (__ballot(same) >> shift0) & gmask;
+      // the distances of the G slots, U gathers in flight
+      float mine = 0.0f;
+      const int32_t jn = min(G, k - r0);
+      for (int32_t j0 = 0; j0 < jn; j0 += U) {
+        RowPart<G, V, NV> eq[U];
+        int32_t qs[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          qs[u] = __shfl(q, (j0 + u) & (G - 1), G);
+          eq[u].load(emb, qs[u], d, lane, j0 + u < jn && qs[u] >= 0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float part = squared(ep, eq[u]);
+          mine = lane == j0 + u ? part : mine;
+          if (grad && j0 + u < jn && ((takes >> (j0 + u)) & 1)) {
+            const float dist = sqrtf(part);
+            const float coef = pair_coef((sames >> (j0 + u)) & 1, dist,
+                                         dist * inv_tau, inv_tau);
+            const bool far = (ones >> (j0 + u)) & 1;
+            any = true;
+#pragma unroll
+            for (int c = 0; c < NV; ++c)
+#pragma unroll
+              for (int v = 0; v < V; ++v) {
+                const float g = coef * (ep.v[c][v] - eq[u].v[c][v]);
+                acc.v[c][v] += g;
+                eq[u].v[c][v] = -g;
+              }
+            // q does not list p: the owner slot gives q its side
+            if (far && coef != 0.0f) add_row(grad, qs[u], d, lane, eq[u]);
+          }
+        }
+      }
+      if (slot) {
+        const float x = sqrtf(mine) * inv_tau;
+        if (take && owner) lsum += (double)pair_term(same, x);
+        const int64_t s = p * k + j;
+        status[s] = (uint16_t)st;
+        if (affinity) affinity[s] = q >= 0 ? expf(-x) : 0.0f;
+        if (sampled) sampled[s] = (take && owner) ? 1 : 0;
+      }
+    }
+    if (any) add_row(grad, p, d, lane, acc);
+  }
+  if (!finite) raise_err(ctl, kErrNonFinite);
+  if (!inside) raise_err(ctl, kErrBadIndex);
+  const unsigned long long te = block_sum(edges, shu);
+  const unsigned long long ti = block_sum(intra, shu);
+  const double tl = block_sum(lsum, shd);
   if (threadIdx.x == 0) {
-    if (e) atomicAdd(&ctl->le_edges, e);
-    if (i) atomicAdd(&ctl->le_intra, i);
+    part_edges[blockIdx.x] = te;
+    part_intra[blockIdx.x] = ti;
+    part_loss[blockIdx.x] = tl;
+  }
+  if (take_all) return;
+  uint32_t *to = hist + ((size_t)(blockIdx.x % kLeCopies) << bits);
+  for (int i = threadIdx.x; i < (1 << bits); i += kLeNT)
+    if (h[i]) atomicAdd(&to[i], h[i]);
+}
+
+// The pair counts, the size of the intra sample, the histogram bin of its
+// largest kept key (sel_prefix) and that key's rank in the bin (sel_rank).
+// sel_mode: 0 no intra pair is kept, 1 all, 2 those up to a threshold.
+constexpr int kLePickNT = 1024;
+
+__global__ __launch_bounds__(kLePickNT) void k_le_pick(
+    Ctl *ctl, const uint32_t *__restrict__ hist, int bits, double rho,
+    int64_t ns, const unsigned long long *__restrict__ part_edges,
+    const unsigned long long *__restrict__ part_intra, int32_t nparts) {
+  __shared__ unsigned long long sh[kLePickNT / kWave];
+  __shared__ int64_t wsum[kLePickNT / kWave];
+  __shared__ int64_t keep;
+  __shared__ bool search;
+  unsigned long long e = 0, a = 0;
+  for (int32_t i = threadIdx.x; i < nparts; i += kLePickNT) {
+    e += part_edges[i];
+    a += part_intra[i];
+  }
+  const unsigned long long edges = block_sum(e, sh);
+  const unsigned long long intra = block_sum(a, sh);
+  if (threadIdx.x == 0) {
+    const int64_t n_intra = (int64_t)intra;
+    const int64_t n_inter = (int64_t)edges - n_intra;
+    int64_t m = n_intra;
+    if (rho < 1.0) {
+      const double cap = floor(
+          __ddiv_rn(__dmul_rn(rho, (double)n_inter), __dsub_rn(1.0, rho)));
+      if (cap < (double)m) m = (int64_t)cap;
+    }
+    keep = m;
+    ctl->le_edges = edges;
+    ctl->le_intra = intra;
+    ctl->le_keep = (unsigned long long)m;
+    const int mode = m == 0 ? 0 : (m == n_intra ? 1 : 2);
+    search = mode == 2;
+    ctl->sel_mode = mode;
+    // a sample of an eighth of the slots or more goes through the rows
+    ctl->sel_dense = rho < 1.0 && m > ns / 8;
+    ctl->sel_prefix = mode == 1 ? ~0ull : 0ull;
+    ctl->sel_rank = 0;
+    ctl->sel_cand = 0;
+  }
+  __syncthreads();
+  const int64_t m = keep;
+  if (!search) return;
+  // bins in order, each thread a contiguous share
+  const int per = ((1 << bits) + kLePickNT - 1) / kLePickNT;
+  int64_t c[(1 << kLeBitsMax) / kLePickNT], s = 0, tot;
+  for (int i = 0; i < (1 << kLeBitsMax) / kLePickNT; ++i) {
+    c[i] = 0;
+    const int b = (int)threadIdx.x * per + i;
+    if (i < per && b < (1 << bits))
+      for (int q = 0; q < kLeCopies; ++q) c[i] += hist[(q << bits) + b];
+    s += c[i];
+  }
+  int64_t before = block_excl_scan<kLePickNT>(s, wsum, &tot);
+  for (int i = 0; i < per; ++i) {
+    if (before <= m - 1 && m - 1 < before + c[i]) {
+      ctl->sel_prefix = (uint64_t)((int)threadIdx.x * per + i);
+      ctl->sel_rank = m - 1 - before;
+      if (c[i] > kLeList) ctl->sel_dense = 1;
+    }
+    before += c[i];
   }
 }
 
-// The size of the intra sample and the selection mode.
-__global__ void k_le_quota(Ctl *ctl, double rho) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const int64_t n_intra = (int64_t)ctl->le_intra;
-  const int64_t n_inter = (int64_t)ctl->le_edges - n_intra;
-  int64_t m = n_intra;
-  if (rho < 1.0) {
-    const double cap =
-        floor(__ddiv_rn(__dmul_rn(rho, (double)n_inter), __dsub_rn(1.0, rho)));
-    if (cap < (double)m) m = (int64_t)cap;
+// Loss and gradient of one sampled intra pair by its owner slot, both sides
+// by atomics; the term is returned in lane 0 of the group.
+template <int G, int V, int NV>
+__device__ __forceinline__ double take_pair(
+    const float *__restrict__ emb, int32_t d, const int32_t *__restrict__ nbr,
+    int32_t k, uint32_t s, float inv_tau, float *grad, uint8_t *sampled,
+    int lane) {
+  const int64_t p = (int64_t)(s / (uint32_t)k);
+  const int64_t q = nbr[s];
+  RowPart<G, V, NV> a, b;
+  a.load(emb, p, d, lane, true);
+  b.load(emb, q, d, lane, true);
+  const float dist = sqrtf(squared(a, b));
+  const float x = dist * inv_tau;
+  const float coef = pair_coef(true, dist, x, inv_tau);
+  if (grad && coef != 0.0f) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c)
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const float g = coef * (a.v[c][v] - b.v[c][v]);
+        a.v[c][v] = g;
+        b.v[c][v] = -g;
+      }
+    add_row(grad, p, d, lane, a);
+    add_row(grad, q, d, lane, b);
   }
-  ctl->le_keep = (unsigned long long)m;
-  ctl->sel_mode = (m == 0) ? 0 : (m == n_intra ? 1 : 2);
-  ctl->sel_prefix = 0;
-  ctl->sel_mask = 0;
-  ctl->sel_rank = m - 1;  // 0-based rank of the largest kept key
+  if (lane != 0) return 0.0;
+  if (sampled) sampled[s] = 1;
+  return (double)pair_term(true, x);
 }
 
 __device__ __forceinline__ uint64_t draw_key(const uint32_t *word, int64_t s) {
   return ((uint64_t)word[s] << 32) | (uint64_t)s;
+}
+
+// The sampled intra pairs below the threshold's bin (all of them in mode 1),
+// found by streaming statuses and words; a block lists a tile's pairs in LDS
+// and its groups of lanes then share them out.  Keys in the bin are listed.
+template <int G, int V, int NV>
+__global__ __launch_bounds__(kLeNT) void k_le_sample(
+    const float *__restrict__ emb, int32_t d, const int32_t *__restrict__ nbr,
+    int32_t k, const uint16_t *__restrict__ status,
+    const uint32_t *__restrict__ word, int64_t ns, float tau, int bits,
+    float *__restrict__ grad, uint8_t *__restrict__ sampled,
+    uint64_t *__restrict__ list, double *__restrict__ part_loss, Ctl *ctl) {
+  __shared__ uint32_t sure[kLeTile];
+  __shared__ uint64_t stage[kLeStage];
+  __shared__ uint32_t n_sure, n_stage, at;
+  __shared__ double shd[kLeNT / kWave];
+  const bool idle = ctl->sel_dense != 0 || ctl->sel_mode == 0;
+  if (idle) {
+    if (threadIdx.x == 0) part_loss[blockIdx.x] = 0.0;
+    return;
+  }
+  const uint64_t bin = ctl->sel_prefix;  // past every bin in mode 1
+  const float inv_tau = 1.0f / tau;
+  const int lane = threadIdx.x & (G - 1);
+  double lsum = 0.0;
+  if (threadIdx.x == 0) n_sure = n_stage = 0;
+  __syncthreads();
+  for (int64_t t0 = (int64_t)blockIdx.x * kLeTile; t0 < ns;
+       t0 += (int64_t)gridDim.x * kLeTile) {
+#pragma unroll
+    for (int j = 0; j < kLeTile / kLeNT; ++j) {
+      const int64_t s = t0 + j * kLeNT + threadIdx.x;
+      if (s < ns && (status[s] & (3 | kSlotOwner)) == (kSlotIntra | kSlotOwner)) {
+        const uint32_t w = word[s];
+        const uint64_t b = w >> (32 - bits);
+        if (b < bin) sure[atomicAdd(&n_sure, 1u)] = (uint32_t)s;
+        else if (b == bin)
+          stage[atomicAdd(&n_stage, 1u)] = ((uint64_t)w << 32) | (uint64_t)s;
+      }
+    }
+    __syncthreads();
+    const uint32_t ne = n_sure, nst = n_stage;
+    for (uint32_t i = threadIdx.x / G; i < ne; i += kLeNT / G)
+      lsum += take_pair<G, V, NV>(emb, d, nbr, k, sure[i], inv_tau, grad,
+                                  sampled, lane);
+    const bool flush = nst > 0 && (nst >= kLeStage - kLeTile ||
+                                   t0 + (int64_t)gridDim.x * kLeTile >= ns);
+    if (flush && threadIdx.x == 0) at = atomicAdd(&ctl->sel_cand, nst);
+    __syncthreads();
+    if (flush)  // the bin holds at most kLeList keys
+      for (uint32_t i = threadIdx.x; i < nst; i += kLeNT)
+        if (at + i < (uint32_t)kLeList) list[at + i] = stage[i];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      n_sure = 0;
+      if (flush) n_stage = 0;
+    }
+    __syncthreads();
+  }
+  const double t = block_sum(lsum, shd);
+  if (threadIdx.x == 0) part_loss[blockIdx.x] = t;
+}
+
+// The sel_rank-th smallest of the listed keys, to sel_prefix: a radix select
+// in LDS, 8 bits a pass, ending once a digit's bin holds one key.
+__global__ __launch_bounds__(kLePickNT) void k_le_select(
+    Ctl *ctl, const uint64_t *__restrict__ list, int bits) {
+  __shared__ uint64_t key[kLeList];
+  __shared__ uint32_t h[256];
+  __shared__ uint32_t wsum[kLePickNT / kWave];
+  __shared__ uint64_t s_prefix, s_mask;
+  __shared__ int64_t s_rank;
+  __shared__ uint32_t s_count;
+  if (ctl->sel_dense != 0 || ctl->sel_mode != 2) return;
+  const uint32_t nc = min(ctl->sel_cand, (uint32_t)kLeList);
+  for (uint32_t i = threadIdx.x; i < nc; i += kLePickNT) key[i] = list[i];
+  if (threadIdx.x == 0) {
+    s_prefix = ctl->sel_prefix << (64 - bits);
+    s_mask = ~0ull << (64 - bits);
+    s_rank = ctl->sel_rank;
+    s_count = nc;
+  }
+  __syncthreads();
+  for (int top = 64 - bits; top > 0 && s_count > 1; top -= 8) {
+    const int shift = top > 8 ? top - 8 : 0;
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
+    __syncthreads();
+    const uint64_t prefix = s_prefix, mask = s_mask;
+    const int64_t rank = s_rank;
+    const uint32_t low = (1u << (top - shift)) - 1;
+    for (uint32_t i = threadIdx.x; i < nc; i += kLePickNT)
+      if ((key[i] & mask) == prefix)
+        atomicAdd(&h[(uint32_t)(key[i] >> shift) & low], 1u);
+    __syncthreads();
+    const uint32_t c = threadIdx.x < 256 ? h[threadIdx.x] : 0u;
+    uint32_t tot;
+    const uint32_t before = block_excl_scan<kLePickNT>(c, wsum, &tot);
+    if (c > 0 && before <= rank && rank < (int64_t)before + c) {
+      s_prefix = prefix | ((uint64_t)threadIdx.x << shift);
+      s_mask = mask | ((uint64_t)low << shift);
+      s_rank = rank - before;
+      s_count = c;
+    }
+    __syncthreads();
+  }
+  // the one key left
+  for (uint32_t i = threadIdx.x; i < nc; i += kLePickNT)
+    if ((key[i] & s_mask) == s_prefix) ctl->sel_prefix = key[i];
+}
+
+// The listed pairs up to the threshold.
+template <int G, int V, int NV>
+__global__ __launch_bounds__(kLeNT) void k_le_listed(
+    const float *__restrict__ emb, int32_t d, const int32_t *__restrict__ nbr,
+    int32_t k, float tau, float *__restrict__ grad,
+    uint8_t *__restrict__ sampled, const uint64_t *__restrict__ list,
+    double *__restrict__ part_loss, const Ctl *ctl) {
+  __shared__ double shd[kLeNT / kWave];
+  double lsum = 0.0;
+  if (ctl->sel_dense == 0 && ctl->sel_mode == 2) {
+    const uint32_t nc = min(ctl->sel_cand, (uint32_t)kLeList);
+    const uint64_t thr = ctl->sel_prefix;
+    const float inv_tau = 1.0f / tau;
+    const int lane = threadIdx.x & (G - 1);
+    for (uint32_t i = (blockIdx.x * kLeNT + threadIdx.x) / G; i < nc;
+         i += gridDim.x * (kLeNT / G))
+      if (list[i] <= thr)
+        lsum += take_pair<G, V, NV>(emb, d, nbr, k, (uint32_t)list[i], inv_tau,
+                                    grad, sampled, lane);
+  }
+  const double t = block_sum(lsum, shd);
+  if (threadIdx.x == 0) part_loss[blockIdx.x] = t;
+}
+
+__global__ __launch_bounds__(kLePickNT) void k_le_total(
+    const double *__restrict__ part, int32_t nparts, Ctl *ctl) {
+  __shared__ double sh[kLePickNT / kWave];
+  double s = 0.0;
+  for (int32_t i = threadIdx.x; i < nparts; i += kLePickNT) s += part[i];
+  s = block_sum(s, sh);
+  if (threadIdx.x == 0) ctl->le_loss = s;
+}
+
+// --- the general selection: radix passes over every slot, then the rows ----
+
+__global__ void k_le_dense_start(Ctl *ctl) {
+  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  ctl->sel_prefix = 0;
+  ctl->sel_mask = 0;
+  ctl->sel_rank = (int64_t)ctl->le_keep - 1;
 }
 
 // One radix-select pass: histogram of the 8-bit digit at `shift` over the
@@ -169,8 +627,8 @@ __global__ __launch_bounds__(kLeNT) void k_le_hist(
 
 // Fixes the digit at `shift` (256 threads, one per digit) and clears the
 // histogram for the next pass.
-__global__ __launch_bounds__(256) void k_le_pick(Ctl *ctl, uint32_t *hist,
-                                                 int shift) {
+__global__ __launch_bounds__(256) void k_le_digit(Ctl *ctl, uint32_t *hist,
+                                                  int shift) {
   __shared__ int64_t wsum[256 / kWave];
   __shared__ int64_t tot;
   const bool live = ctl->sel_mode == 2;
@@ -187,142 +645,77 @@ __global__ __launch_bounds__(256) void k_le_pick(Ctl *ctl, uint32_t *hist,
   }
 }
 
-// Affinity of every slot; loss and gradient of every sampled pair.  G lanes
-// per row (G >= k), NV dimensions per lane (D <= G * NV).  Lane t first reads
-// slot t of the row (id and status, one coalesced load), then the group walks
-// the slots U at a time, with the U embedding gathers issued together.
-constexpr int kLeU = 4;
-
-template <int G, int NV>
-__global__ __launch_bounds__(kLeNT) void k_le_rows(
+// Loss and gradient of the sampled intra pairs, a group of lanes a row; a
+// mirror slot reads its owner's word, so that only one-sided pairs need
+// atomics on the far row.
+template <int G, int V, int NV>
+__global__ __launch_bounds__(kLeNT) void k_le_dense(
     const float *__restrict__ emb, int32_t n, int32_t d,
     const int32_t *__restrict__ nbr, int32_t k,
     const uint16_t *__restrict__ status, const uint32_t *__restrict__ word,
-    float tau, const Ctl *sel, float *__restrict__ affinity,
-    float *__restrict__ grad, uint8_t *__restrict__ sampled, Ctl *ctl) {
-  __shared__ double sh[kLeNT / kWave];
-  constexpr int kRows = kLeNT / G;  // rows per block and step
+    float tau, float *__restrict__ grad, uint8_t *__restrict__ sampled,
+    double *__restrict__ part_loss, const Ctl *ctl) {
+  constexpr int kRows = kLeNT / G;
+  __shared__ double shd[kLeNT / kWave];
   const int lane = threadIdx.x & (G - 1);
-  const int mode = sel->sel_mode;
-  const uint64_t thr = sel->sel_prefix;
+  const int shift0 = (int)(threadIdx.x & (kWave - 1) & ~(G - 1));
+  const uint64_t gmask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1);
+  const bool all = ctl->sel_mode == 1;
+  const uint64_t thr = ctl->sel_prefix;
   const float inv_tau = 1.0f / tau;
   double lsum = 0.0;
   for (int64_t p = (int64_t)blockIdx.x * kRows + threadIdx.x / G; p < n;
        p += (int64_t)gridDim.x * kRows) {
-    const int32_t my_q = lane < k ? nbr[p * k + lane] : -1;
-    const int32_t my_st = lane < k ? (int32_t)status[p * k + lane] : 0;
-    float ep[NV], acc[NV];
+    RowPart<G, V, NV> ep, acc;
+    ep.load(emb, p, d, lane, true);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int i = lane + v * G;
-      ep[v] = i < d ? emb[p * d + i] : 0.0f;
-      acc[v] = 0.0f;
-    }
-    for (int32_t j0 = 0; j0 < k; j0 += kLeU) {
-      int32_t qs[kLeU];
-      float eq[kLeU][NV];
+    for (int c = 0; c < NV; ++c)
 #pragma unroll
-      for (int u = 0; u < kLeU; ++u) {
-        const int32_t q = __shfl(my_q, j0 + u, G);
-        qs[u] = (j0 + u < k && q >= 0 && q < n) ? q : -1;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const int i = lane + v * G;
-          eq[u][v] = (qs[u] >= 0 && i < d) ? emb[(int64_t)qs[u] * d + i] : 0.0f;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kLeU; ++u) {
-        const int32_t j = j0 + u;
-        if (j >= k) break;
-        const int64_t s = p * k + j;
-        const int32_t q = qs[u];
-        const uint16_t st = (uint16_t)__shfl(my_st, j, G);
-        if (q < 0) {  // empty slot (bad ids were reported already)
-          if (lane == 0) {
-            if (affinity) affinity[s] = 0.0f;
-            if (sampled) sampled[s] = 0;
-          }
-          continue;
-        }
-        float df[NV];
-        float part = 0.0f;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          df[v] = ep[v] - eq[u][v];
-          part += df[v] * df[v];
-        }
-#pragma unroll
-        for (int off = G / 2; off > 0; off >>= 1)
-          part += __shfl_xor(part, off, G);
+      for (int v = 0; v < V; ++v) acc.v[c][v] = 0.0f;
+    bool any = false;
+    for (int32_t r0 = 0; r0 < k; r0 += G) {
+      const int32_t j = r0 + lane;
+      const int64_t s = p * k + j;
+      const uint32_t st = j < k ? status[s] : 0u;
+      const int32_t q = j < k ? nbr[s] : -1;
+      const bool owner = (st & kSlotOwner) != 0;
+      bool take = (st & 3) == kSlotIntra;
+      if (take && !all)
+        take = draw_key(word, owner ? s : (int64_t)q * k + (st >> 8)) <= thr;
+      uint64_t takes = (__ballot(take) >> shift0) & gmask;
+      const uint64_t ones = (__ballot(!(st & kSlotMutual)) >> shift0) & gmask;
+      float mine = 0.0f;
+      while (takes) {
+        const int u = __ffsll((unsigned long long)takes) - 1;
+        takes &= takes - 1;
+        const int32_t qu = __shfl(q, u, G);
+        RowPart<G, V, NV> eq;
+        eq.load(emb, qu, d, lane, true);
+        const float part = squared(ep, eq);
+        mine = lane == u ? part : mine;
+        if (!grad) continue;
         const float dist = sqrtf(part);
-        const float x = dist * inv_tau;
-        bool take = false;
-        const int type = st & 3;
-        if (type == kSlotInter) {
-          take = true;
-        } else if (type == kSlotIntra) {
-          const int64_t os =
-              (st & kSlotOwner) ? s : (int64_t)q * k + (st >> 8);
-          take = mode == 1 || (mode == 2 && draw_key(word, os) <= thr);
-        }
-        const bool owner = (st & kSlotOwner) != 0;
-        if (lane == 0) {
-          if (affinity) affinity[s] = expf(-x);
-          if (sampled) sampled[s] = (take && owner) ? 1 : 0;
-        }
-        if (!take) continue;
-        float term, coef;
-        if (type == kSlotIntra) {
-          term = x;
-          coef = dist > 0.0f ? inv_tau / dist : 0.0f;
-        } else {
-          term = -logf(-expm1f(-x));
-          coef = dist > 0.0f ? -inv_tau / (expm1f(x) * dist) : 0.0f;
-        }
-        if (owner && lane == 0) lsum += (double)term;
-        if (grad) {
+        const float coef = pair_coef(true, dist, dist * inv_tau, inv_tau);
+        any = true;
 #pragma unroll
-          for (int v = 0; v < NV; ++v) acc[v] += coef * df[v];
-          if (!(st & kSlotMutual) && coef != 0.0f) {
-            // q does not list p: the owner slot gives q its side
+        for (int c = 0; c < NV; ++c)
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-              const int i = lane + v * G;
-              if (i < d)
-                unsafeAtomicAdd(grad + (int64_t)q * d + i, -coef * df[v]);
-            }
+          for (int v = 0; v < V; ++v) {
+            const float g = coef * (ep.v[c][v] - eq.v[c][v]);
+            acc.v[c][v] += g;
+            eq.v[c][v] = -g;
           }
-        }
+        if (((ones >> u) & 1) && coef != 0.0f) add_row(grad, qu, d, lane, eq);
+      }
+      if (take && owner) {
+        lsum += (double)pair_term(true, sqrtf(mine) * inv_tau);
+        if (sampled) sampled[s] = 1;
       }
     }
-    if (grad) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const int i = lane + v * G;
-        if (i < d && acc[v] != 0.0f) unsafeAtomicAdd(grad + p * d + i, acc[v]);
-      }
-    }
+    if (any) add_row(grad, p, d, lane, acc);
   }
-  const double t = block_sum(lsum, sh);
-  if (threadIdx.x == 0 && t != 0.0) atomicAdd(&ctl->le_loss, t);
-}
-
-template <int G, int NV>
-void launch_rows(const LossArgs &g, const uint16_t *status, Ctl *ctl,
-                 hipStream_t st) {
-  constexpr int kRows = kLeNT / G;
-  int64_t blocks = ((int64_t)g.n + kRows - 1) / kRows;
-  if (blocks > 16384) blocks = 16384;
-  hipLaunchKernelGGL((k_le_rows<G, NV>), dim3((unsigned)blocks), dim3(kLeNT),
-                     0, st, g.emb, g.n, g.d, g.nbr, g.k, status, g.word,
-                     (float)g.tau, ctl, g.affinity, g.grad, g.sampled, ctl);
-}
-
-__global__ __launch_bounds__(256) void k_fill0(float *x, int64_t count) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count;
-       i += (int64_t)gridDim.x * blockDim.x)
-    x[i] = 0.0f;
+  const double t = block_sum(lsum, shd);
+  if (threadIdx.x == 0) part_loss[blockIdx.x] = t;
 }
 
 unsigned grid_for(int64_t items) {
@@ -330,56 +723,159 @@ unsigned grid_for(int64_t items) {
   return (unsigned)(b < kLeGrid ? (b < 1 ? 1 : b) : kLeGrid);
 }
 
+// Workspace of one call.
+struct LossWork {
+  uint16_t *status;
+  uint32_t *hist;
+  uint64_t *list;
+  unsigned long long *part_edges, *part_intra;
+  double *part_loss;  // k_le_pairs, then k_le_sample or k_le_dense, then
+                      // k_le_listed: kLeGrid each
+};
+
+LossWork take_work(Arena &a, int64_t ns) {
+  LossWork w;
+  w.status = a.take<uint16_t>((size_t)ns);
+  w.hist = a.take<uint32_t>((size_t)kLeCopies << kLeBitsMax);
+  w.list = a.take<uint64_t>(kLeList);
+  w.part_edges = a.take<unsigned long long>(kLeGrid);
+  w.part_intra = a.take<unsigned long long>(kLeGrid);
+  w.part_loss = a.take<double>(3 * kLeGrid);
+  return w;
+}
+
+// The kernels of one row layout.
+template <int G, int V, int NV>
+struct Rows {
+  static unsigned blocks(int64_t n) { return grid_for(n * G); }
+
+  static void pairs(const LossArgs &g, const LossWork &w, int bits, Ctl *ctl,
+                    hipStream_t st) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(g.nbr);
+    const dim3 grid(blocks(g.n));
+#define EZSP_PAIRS(VN)                                                        \
+  hipLaunchKernelGGL((k_le_pairs<G, V, NV, VN>), grid, dim3(kLeNT), 0, st,    \
+                     g.emb, g.n, g.d, g.nbr, g.k, g.cls, g.word,              \
+                     (float)g.tau, g.rho >= 1.0, bits, w.status, g.affinity,  \
+                     g.grad, g.sampled, w.hist, w.part_edges, w.part_intra,   \
+                     w.part_loss, ctl)
+    if (g.k % 4 == 0 && (at & 15) == 0) EZSP_PAIRS(4);
+    else if (g.k % 2 == 0 && (at & 7) == 0) EZSP_PAIRS(2);
+    else EZSP_PAIRS(1);
+#undef EZSP_PAIRS
+  }
+
+  // the sample by list; returns the blocks whose loss parts are written
+  static void sample(const LossArgs &g, const LossWork &w, int bits, Ctl *ctl,
+                     unsigned sb, unsigned lb, hipStream_t st) {
+    const int64_t ns = (int64_t)g.n * g.k;
+    const unsigned pb = blocks(g.n);
+    hipLaunchKernelGGL((k_le_sample<G, V, NV>), dim3(sb), dim3(kLeNT), 0, st,
+                       g.emb, g.d, g.nbr, g.k, w.status, g.word, ns,
+                       (float)g.tau, bits, g.grad, g.sampled, w.list,
+                       w.part_loss + pb, ctl);
+    hipLaunchKernelGGL(k_le_select, dim3(1), dim3(kLePickNT), 0, st, ctl,
+                       w.list, bits);
+    hipLaunchKernelGGL((k_le_listed<G, V, NV>), dim3(lb), dim3(kLeNT), 0, st,
+                       g.emb, g.d, g.nbr, g.k, (float)g.tau, g.grad,
+                       g.sampled, w.list, w.part_loss + pb + sb, ctl);
+  }
+
+  static void dense(const LossArgs &g, const LossWork &w, Ctl *ctl,
+                    hipStream_t st) {
+    const unsigned pb = blocks(g.n);
+    hipLaunchKernelGGL((k_le_dense<G, V, NV>), dim3(pb), dim3(kLeNT), 0, st,
+                       g.emb, g.n, g.d, g.nbr, g.k, w.status, g.word,
+                       (float)g.tau, g.grad, g.sampled, w.part_loss + pb, ctl);
+  }
+};
+
+template <class R>
+int run_rows(const LossArgs &g, const LossWork &w, Ctl *ctl, Ctl *hc,
+             hipStream_t st) {
+  const int64_t ns = (int64_t)g.n * g.k;
+  const int bits = hist_bits(ns);
+  const unsigned pb = R::blocks(g.n);
+  const int64_t tiles = (ns + kLeTile - 1) / kLeTile;
+  const unsigned sb = (unsigned)(tiles < kLeGrid ? tiles : kLeGrid);
+  const unsigned lb = 64;
+  prof_begin("edge_loss", st);
+  hipLaunchKernelGGL(k_le_clear,
+                     dim3(grid_for(g.grad ? (int64_t)g.n * g.d / 4 + 1 : 4096)),
+                     dim3(kLeNT), 0, st, g.grad, (int64_t)g.n * g.d, w.hist,
+                     kLeCopies << bits);
+  R::pairs(g, w, bits, ctl, st);
+  hipLaunchKernelGGL(k_le_pick, dim3(1), dim3(kLePickNT), 0, st, ctl, w.hist,
+                     bits, g.rho, ns, w.part_edges, w.part_intra, (int32_t)pb);
+  unsigned parts = pb;
+  if (g.rho < 1.0) {
+    R::sample(g, w, bits, ctl, sb, lb, st);
+    parts += sb + lb;
+  }
+  hipLaunchKernelGGL(k_le_total, dim3(1), dim3(kLePickNT), 0, st, w.part_loss,
+                     (int32_t)parts, ctl);
+  prof_end(st);
+  int rc = read_ctl(ctl, hc, st);
+  if (rc || hc->err || !hc->sel_dense) return rc;
+  prof_begin("edge_loss", st);
+  hipLaunchKernelGGL(k_le_dense_start, dim3(1), dim3(64), 0, st, ctl);
+  hipLaunchKernelGGL(k_le_clear, dim3(1), dim3(kLeNT), 0, st, (float *)nullptr,
+                     (int64_t)0, w.hist, 256);
+  for (int shift = 56; shift >= 0 && hc->sel_mode == 2; shift -= 8) {
+    hipLaunchKernelGGL(k_le_hist, dim3(grid_for(ns)), dim3(kLeNT), 0, st,
+                       w.status, g.word, ns, shift, ctl, w.hist);
+    hipLaunchKernelGGL(k_le_digit, dim3(1), dim3(256), 0, st, ctl, w.hist,
+                       shift);
+  }
+  R::dense(g, w, ctl, st);
+  hipLaunchKernelGGL(k_le_total, dim3(1), dim3(kLePickNT), 0, st, w.part_loss,
+                     (int32_t)(2 * pb), ctl);
+  prof_end(st);
+  return read_ctl(ctl, hc, st);
+}
+
 }  // namespace
 
 void loss_reserve(Arena &a, int32_t n, int32_t k) {
-  a.take<uint16_t>((size_t)n * k);
-  a.take<uint32_t>(256);
+  take_work(a, (int64_t)n * k);
 }
 
 int loss_run(const LossArgs &g, LossResult *res, Ctl *ctl, Arena &a,
              hipStream_t st) {
   const int64_t ns = (int64_t)g.n * g.k;
-  uint16_t *status = a.take<uint16_t>((size_t)ns);
-  uint32_t *hist = a.take<uint32_t>(256);
+  const LossWork w = take_work(a, ns);
   Ctl *hc = pinned_ctl();
   if (!hc) {
     set_error("hipHostMalloc of the control block failed");
     return -5;
   }
-  prof_begin("edge_loss", st);
-  hipLaunchKernelGGL(k_fill0, dim3(1), dim3(256), 0, st,
-                     reinterpret_cast<float *>(hist), (int64_t)256);
-  if (g.grad)
-    hipLaunchKernelGGL(k_fill0, dim3(grid_for((int64_t)g.n * g.d)), dim3(256),
-                       0, st, g.grad, (int64_t)g.n * g.d);
-  hipLaunchKernelGGL(k_maxabs, dim3(2048), dim3(256), 0, st, g.emb,
-                     (int64_t)g.n * g.d, ctl);
-  if (g.k % 4 == 0 && (reinterpret_cast<uintptr_t>(g.nbr) & 15) == 0)
-    hipLaunchKernelGGL(k_le_classify<true>, dim3(grid_for(ns)), dim3(kLeNT),
-                       0, st, g.nbr, g.n, g.k, g.cls, status, ctl);
-  else
-    hipLaunchKernelGGL(k_le_classify<false>, dim3(grid_for(ns)), dim3(kLeNT),
-                       0, st, g.nbr, g.n, g.k, g.cls, status, ctl);
-  hipLaunchKernelGGL(k_le_quota, dim3(1), dim3(64), 0, st, ctl, g.rho);
-  for (int shift = 56; shift >= 0; shift -= 8) {
-    hipLaunchKernelGGL(k_le_hist, dim3(grid_for(ns)), dim3(kLeNT), 0, st,
-                       status, g.word, ns, shift, ctl, hist);
-    hipLaunchKernelGGL(k_le_pick, dim3(1), dim3(256), 0, st, ctl, hist, shift);
+  // 16-byte vectors where every row starts at one; lanes a row: the power
+  // of two that covers D, from 4 to 64
+  const bool vec = g.d % 4 == 0 &&
+                   (reinterpret_cast<uintptr_t>(g.emb) & 15) == 0;
+  const int32_t lanes = vec ? g.d / 4 : g.d;
+  int rc;
+#define EZSP_LE(G, V, NV) rc = run_rows<Rows<G, V, NV>>(g, w, ctl, hc, st)
+  if (vec) {
+    if (lanes <= 4) EZSP_LE(4, 4, 1);
+    else if (lanes <= 8) EZSP_LE(8, 4, 1);
+    else if (lanes <= 16) EZSP_LE(16, 4, 1);
+    else if (lanes <= 32) EZSP_LE(32, 4, 1);
+    else if (lanes <= 64) EZSP_LE(64, 4, 1);
+    else if (lanes <= 128) EZSP_LE(64, 4, 2);
+    else EZSP_LE(64, 4, 4);
+  } else {
+    if (lanes <= 4) EZSP_LE(4, 1, 1);
+    else if (lanes <= 8) EZSP_LE(8, 1, 1);
+    else if (lanes <= 16) EZSP_LE(16, 1, 1);
+    else if (lanes <= 32) EZSP_LE(32, 1, 1);
+    else if (lanes <= 64) EZSP_LE(64, 1, 1);
+    else if (lanes <= 128) EZSP_LE(64, 1, 2);
+    else if (lanes <= 256) EZSP_LE(64, 1, 4);
+    else if (lanes <= 512) EZSP_LE(64, 1, 8);
+    else EZSP_LE(64, 1, 16);
   }
-  // lanes per row: the power of two covering both D (up to 64) and k
-  const int32_t span = g.d < 64 ? (g.d > g.k ? g.d : g.k) : 64;
-  if (span <= 4) launch_rows<4, 1>(g, status, ctl, st);
-  else if (span <= 8) launch_rows<8, 1>(g, status, ctl, st);
-  else if (span <= 16) launch_rows<16, 1>(g, status, ctl, st);
-  else if (span <= 32) launch_rows<32, 1>(g, status, ctl, st);
-  else if (g.d <= 64) launch_rows<64, 1>(g, status, ctl, st);
-  else if (g.d <= 128) launch_rows<64, 2>(g, status, ctl, st);
-  else if (g.d <= 256) launch_rows<64, 4>(g, status, ctl, st);
-  else if (g.d <= 512) launch_rows<64, 8>(g, status, ctl, st);
-  else launch_rows<64, 16>(g, status, ctl, st);
-  prof_end(st);
-  int rc = read_ctl(ctl, hc, st);
+#undef EZSP_LE
   if (rc) return rc;
   // algorithmic bytes: every input read once (embeddings, table, words,
   // classes) and every output written once

@@ -215,6 +215,8 @@ __global__ void k_ctl_init(Ctl *ctl) {
     ctl->sel_prefix = 0;
     ctl->sel_mask = 0;
     ctl->sel_rank = 0;
+    ctl->sel_cand = 0;
+    ctl->sel_dense = 0;
     ctl->le_edges = 0;
     ctl->le_intra = 0;
     ctl->le_keep = 0;
