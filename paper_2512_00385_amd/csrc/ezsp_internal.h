@@ -42,6 +42,26 @@ __device__ __forceinline__ bool xcd_item(int32_t m, int32_t &c) {
   return j < per && c < m;
 }
 
+// Folds the striped bounding box (k_bbox) in a block of at least 192
+// threads: box[0..2] the minima, box[3..5] the maxima, in ordered-int form.
+// A kernel whose blocks do this themselves needs no fold launched before it.
+// Contains a barrier; box is LDS.
+__device__ __forceinline__ void fold_box(const Ctl *ctl, int32_t *box) {
+  static_assert(kStripes == 32, "a half-wave per bound");
+  const int t = threadIdx.x;
+  if (t < 6 * kStripes) {
+    const int a = t / kStripes;
+    int32_t v = ctl->bbox_s[a][t % kStripes].v;
+#pragma unroll
+    for (int off = kStripes / 2; off > 0; off >>= 1) {
+      const int32_t o = __shfl_xor(v, off, kStripes);
+      v = a < 3 ? min(v, o) : max(v, o);
+    }
+    if (t % kStripes == 0) box[a] = v;
+  }
+  __syncthreads();
+}
+
 // Row stride of the internal neighbour tables: k rounded up to a multiple
 // of 4 (16-byte rows for vector loads), padded with -1.
 __host__ __device__ __forceinline__ int32_t pad4(int32_t k) {
