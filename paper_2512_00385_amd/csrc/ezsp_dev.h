@@ -67,15 +67,14 @@ struct Ctl {
   int32_t n_cbig;       // components whose table window exceeds one chunk
   int32_t n_tiles;      // member tiles of those components
   int32_t tail_level;   // level that reached max_rounds in the tail kernel
-  int64_t cut_w2;       // 2 * cut weight (directed sum) of the current graph
-  double fid_total;     // fidelity term of the energy
   Stripe e_next_s[kStripes];  // device side of e_next
   Stripe e_fwd_s[kStripes];   // device side of e_fwd
   Stripe maxabs_s[kStripes];  // max |e| bits from the fused gather
   Stripe bbox_s[6][kStripes]; // bbox_enc's min xyz, max xyz per stripe
                               // (folded into bbox_enc by k_bbox_fold)
   int32_t tail_nc[16];        // superpoints of every level the tail ended
-  int64_t tail_cut2[16];      // ... and 2 x their cut weight
+  int64_t tail_cut2[16];      // 2 x the cut weight of every level
+  double lvl_fid[16];         // its fidelity term
   // linking of isolated nodes
   uint32_t maxabs_x_bits;     // max |coordinate| as fp32 bits
   int32_t Fx;                 // fixed-point shift of the positions

@@ -2188,38 +2188,64 @@ __global__ __launch_bounds__(256) void k_iota(int32_t n, int32_t *out) {
 
 constexpr int kEnergyBlocks = 1024;
 
+// Levels whose fidelity one launch sums (blockIdx.y): the node of a point is
+// M, then map (level stride nt, null for none), its means mu (level stride
+// nt * d), nc components (null: nc0).
+struct EnergyLevels {
+  const int32_t *M, *map;
+  const double *mu;
+  const int32_t *nc;
+  int32_t nt, nc0, level0;
+};
+
 // Fidelity term sum_p |e_p - Y_P(p)|^2 in the direct form; per-block partial
-// sums in a fixed order, so the result is reproducible.
-template <bool FIRST>
+// sums in a fixed order, so the result is reproducible.  V dimensions a
+// thread and step (4 when d is a multiple of it: one node lookup and 16-byte
+// loads for four terms).
+template <bool FIRST, int V>
 __global__ __launch_bounds__(256) void k_energy_fid(int32_t n, int32_t d,
-                                                    int32_t nc,
                                                     const float *emb,
-                                                    const int32_t *M,
-                                                    const int32_t *Mt,
-                                                    int32_t nt,
-                                                    const double *mu,
+                                                    EnergyLevels e,
                                                     const Ctl *ctl,
                                                     double *partial) {
   __shared__ double ws[256 / kWave];
+  const int32_t l = e.level0 + (int32_t)blockIdx.y;
+  const int32_t *map = e.map ? e.map + (int64_t)l * e.nt : nullptr;
+  const double *mu = e.map ? e.mu + (int64_t)l * e.nt * d : e.mu;
+  const int32_t nc = e.nc ? min(e.nc[l], e.nt) : e.nc0;
   const double sF = ldexp(1.0, ctl->F), sIF = ldexp(1.0, -ctl->F);
   double acc = 0.0;
-  const int64_t total = (int64_t)n * d;
+  const int32_t dv = d / V;
+  const int64_t total = (int64_t)n * dv;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
        t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = t / d;
-    const int32_t j = (int32_t)(t - i * d);
-    const double e = (double)emb[t];
-    double m;
-    if (FIRST) {
-      m = rint(e * sF) * sIF;
+    const int64_t i = t / dv;
+    const int32_t j = (int32_t)(t - i * dv) * V;
+    double x[V], m[V];
+    if (V == 4) {
+      const float4 f = reinterpret_cast<const float4 *>(emb)[t];
+      x[0] = f.x;
+      x[1 % V] = f.y;
+      x[2 % V] = f.z;
+      x[3 % V] = f.w;
     } else {
-      int32_t c = M[i];
-      if (Mt) c = ((uint32_t)c < (uint32_t)nt) ? Mt[c] : -1;
-      m = ((uint32_t)c < (uint32_t)nc) ? mu[(int64_t)c * d + j] : 0.0;
+      x[0] = (double)emb[t];
     }
-    const double r = e - m;
-    const double sq = r * r;
-    acc = acc + sq;
+    if (FIRST) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) m[v] = rint(x[v] * sF) * sIF;
+    } else {
+      int32_t c = e.M[i];
+      if (map) c = ((uint32_t)c < (uint32_t)e.nt) ? map[c] : -1;
+      const bool in = (uint32_t)c < (uint32_t)nc;
+#pragma unroll
+      for (int v = 0; v < V; ++v) m[v] = in ? mu[(int64_t)c * d + j + v] : 0.0;
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const double r = x[v] - m[v];
+      acc = acc + r * r;
+    }
   }
   for (int off = kWave / 2; off > 0; off >>= 1)
     acc += __shfl_xor(acc, off, kWave);
@@ -2228,35 +2254,56 @@ __global__ __launch_bounds__(256) void k_energy_fid(int32_t n, int32_t d,
   if (threadIdx.x == 0) {
     double b = 0.0;
     for (int q = 0; q < 256 / kWave; ++q) b += ws[q];
-    partial[blockIdx.x] = b;
+    partial[blockIdx.y * kEnergyBlocks + blockIdx.x] = b;
   }
 }
 
-__global__ void k_energy_sum(const double *partial, int32_t nb, Ctl *ctl) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// A block per level adds the partial sums (one thread took 57 us for 1024).
+__global__ __launch_bounds__(256) void k_energy_sum(const double *partial,
+                                                    int32_t level0, Ctl *ctl) {
+  __shared__ double ws[256 / kWave];
+  const double *mine = partial + blockIdx.x * kEnergyBlocks;
   double s = 0.0;
-  for (int32_t b = 0; b < nb; ++b) s += partial[b];
-  ctl->fid_total = s;
+  for (int32_t b = threadIdx.x; b < kEnergyBlocks; b += 256) s += mine[b];
+  s = wave_sum(s);
+  if ((threadIdx.x & (kWave - 1)) == 0) ws[threadIdx.x / kWave] = s;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int q = 1; q < 256 / kWave; ++q) s += ws[q];
+  ctl->lvl_fid[level0 + (int32_t)blockIdx.x] = s;
 }
 
-// Sum of the weights of all rows (both directions of every edge).
+void launch_energy(bool first, int32_t n, int32_t d, const float *emb,
+                   const EnergyLevels &e, int32_t levels, Ctl *ctl,
+                   double *partial, hipStream_t st) {
+  const dim3 grid(kEnergyBlocks, (unsigned)levels);
+#define EZSP_FID(FIRST, V)                                                   \
+  hipLaunchKernelGGL((k_energy_fid<FIRST, V>), grid, dim3(256), 0, st, n, d, \
+                     emb, e, ctl, partial)
+  if (first) {
+    if (d % 4 == 0) EZSP_FID(true, 4);
+    else EZSP_FID(true, 1);
+  } else {
+    if (d % 4 == 0) EZSP_FID(false, 4);
+    else EZSP_FID(false, 1);
+  }
+#undef EZSP_FID
+  hipLaunchKernelGGL(k_energy_sum, dim3((unsigned)levels), dim3(256), 0, st,
+                     partial, e.level0, ctl);
+}
+
+// Sum of the weights of all rows (both directions of every edge), for level
+// l's cut.
 __global__ __launch_bounds__(256) void k_weight_sum(int32_t nn, Adj a,
-                                                    Ctl *ctl) {
+                                                    int32_t l, Ctl *ctl) {
   long long acc = 0;
   for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nn;
        v += gridDim.x * blockDim.x)
     for_row<false>(a, v, 0, 1, [&](int32_t, int32_t w) { acc += w; });
   acc = wave_sum(acc);
   if ((threadIdx.x & (kWave - 1)) == 0 && acc)
-    atomicAdd(reinterpret_cast<unsigned long long *>(&ctl->cut_w2),
+    atomicAdd(reinterpret_cast<unsigned long long *>(&ctl->tail_cut2[l]),
               (unsigned long long)acc);
-}
-
-__global__ void k_energy_reset(Ctl *ctl) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    ctl->cut_w2 = 0;
-    ctl->fid_total = 0.0;
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -3324,7 +3371,8 @@ struct ScanLinkWin {
 // Cut weight of the input graph (Eq. gmpp's second term on E0) for the
 // point -> node map M: both directions of every first-round edge.
 __global__ __launch_bounds__(256) void k_cut_e0(int32_t n, Adj a0,
-                                                const int32_t *M, Ctl *ctl) {
+                                                const int32_t *M, int32_t l,
+                                                Ctl *ctl) {
   long long acc = 0;
   for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n;
        v += gridDim.x * blockDim.x) {
@@ -3335,7 +3383,7 @@ __global__ __launch_bounds__(256) void k_cut_e0(int32_t n, Adj a0,
   }
   acc = wave_sum(acc);
   if ((threadIdx.x & (kWave - 1)) == 0 && acc)
-    atomicAdd(reinterpret_cast<unsigned long long *>(&ctl->cut_w2),
+    atomicAdd(reinterpret_cast<unsigned long long *>(&ctl->tail_cut2[l]),
               (unsigned long long)acc);
 }
 
@@ -4123,7 +4171,7 @@ void carve(Arena &a, int32_t n, int32_t d, int32_t k, bool link, Bufs *b) {
   b->lvl_mu = a.take<double>((size_t)kTailLevels * b->nt * d);
   b->bsum = a.take<int32_t>(scan_blocks(ed + n1) + 2);
   b->tmp = a.take<int32_t>(8);
-  b->partial = a.take<double>(kEnergyBlocks);
+  b->partial = a.take<double>(kTailLevels * kEnergyBlocks);
   b->link = link;
   b->pts = nullptr;
   b->lk_sx[0] = b->lk_sx[1] = nullptr;
@@ -4592,8 +4640,21 @@ int incr_compact(const Bufs &b, Adj &adj, int &cur, int32_t n, int32_t &nn,
 
 // The rest of the ladder in the tail kernel, then the labels (and energy)
 // of every level it ended.
+// The levels' energies from the control block read last: fidelity plus
+// lambda times the cut, cut0[l] / 2 where that is not negative (twice the
+// edges of the input graph, for a level without a merge).
+void fill_energy(const LadderArgs &g, const Ctl *h, const int64_t *cut0) {
+  if (!g.want_energy || !g.energy) return;
+  for (int32_t l = 0; l < g.n_levels; ++l) {
+    const int64_t cut2 = cut0[l] >= 0 ? cut0[l] : h->tail_cut2[l];
+    const double cut = (double)(cut2 / 2);
+    const double reg = g.lambdas[l] * cut;
+    g.energy[l] = h->lvl_fid[l] + reg;
+  }
+}
+
 int run_tail(const LadderArgs &g, const Bufs &b, const float *emb,
-             const Adj &adj, int cur, int32_t nn, int32_t ed, int32_t level0,
+             const int64_t *cut0, const Adj &adj, int cur, int32_t nn, int32_t ed, int32_t level0,
              int32_t round0, int32_t max_rounds, Ctl *ctl, Ctl *h,
              hipStream_t st) {
   const int32_t n = g.n, d = g.d;
@@ -4664,10 +4725,14 @@ int run_tail(const LadderArgs &g, const Bufs &b, const float *emb,
   hipLaunchKernelGGL(k_tail_labels, blocks_for(n), dim3(256), 0, st, n, g.inv,
                      b.M, b.lvl_map, b.lvl_rank, t.lvl_nc, nn, level0,
                      g.n_levels, g.labels, ctl);
+  if (t.want_energy)
+    launch_energy(false, n, d, emb,
+                  EnergyLevels{b.M, b.lvl_map, b.lvl_mu, t.lvl_nc, nn, 0,
+                               level0},
+                  g.n_levels - level0, ctl, b.partial, st);
   int rc = read_ctl(ctl, h, st);
   if (rc) return rc;
   const int32_t *nc = h->tail_nc;
-  const int64_t *cut2 = h->tail_cut2;
   if (h->err & kErrNotConv) {
     set_error("level %d reached max_rounds = %d", h->tail_level, max_rounds);
     return -6;
@@ -4680,23 +4745,7 @@ int run_tail(const LadderArgs &g, const Bufs &b, const float *emb,
     }
     g.n_comp[l] = nc[l];
   }
-  if (t.want_energy) {
-    for (int32_t l = level0; l < g.n_levels; ++l) {
-      // level snapshots have a stride of the tail's start size nn
-      const int32_t *map = b.lvl_map + (int64_t)l * nn;
-      hipLaunchKernelGGL(k_energy_reset, dim3(1), dim3(64), 0, st, ctl);
-      hipLaunchKernelGGL(k_energy_fid<false>, dim3(kEnergyBlocks), dim3(256),
-                         0, st, n, d, nc[l], emb, b.M, map, nn,
-                         b.lvl_mu + (int64_t)l * nn * d, ctl, b.partial);
-      hipLaunchKernelGGL(k_energy_sum, dim3(1), dim3(64), 0, st, b.partial,
-                         kEnergyBlocks, ctl);
-      if ((rc = read_ctl(ctl, h, st))) return rc;
-      if (h->err) return status_from_err(h->err);
-      const double cut = (double)(cut2[l] / 2);
-      const double reg = g.lambdas[l] * cut;
-      g.energy[l] = h->fid_total + reg;
-    }
-  }
+  fill_energy(g, h, cut0);
   return 0;
 }
 
@@ -4915,6 +4964,8 @@ int ladder_run(const LadderArgs &g, Ctl *ctl, Arena &a, hipStream_t st) {
   if (const char *e = getenv("EZSP_INCR_COMPACT_EVERY"))
     compact_every = (int32_t)std::max<long>(0, strtol(e, nullptr, 10));
   const int64_t tcap = 2 * edge_bound(n, k);
+  int64_t cut0[kTailLevels];
+  for (int64_t &c : cut0) c = -1;
   for (int32_t l = 0; l < g.n_levels; ++l) {
     const double lambda = g.lambdas[l];
     const int64_t smin = g.min_size ? g.min_size[l] : 0;
@@ -5089,38 +5140,27 @@ int ladder_run(const LadderArgs &g, Ctl *ctl, Arena &a, hipStream_t st) {
     }
     g.n_comp[l] = nn;
     if (g.want_energy && g.energy) {
-      hipLaunchKernelGGL(k_energy_reset, dim3(1), dim3(64), 0, st, ctl);
+      launch_energy(first, n, d, emb,
+                    EnergyLevels{b.M, nullptr, b.mu, nullptr, 0, nn, l}, 1,
+                    ctl, b.partial, st);
       if (first)
-        hipLaunchKernelGGL(k_energy_fid<true>, dim3(kEnergyBlocks), dim3(256),
-                           0, st, n, d, nn, emb, b.M, (const int32_t *)nullptr,
-                           0, b.mu, ctl, b.partial);
-      else
-        hipLaunchKernelGGL(k_energy_fid<false>, dim3(kEnergyBlocks),
-                           dim3(256), 0, st, n, d, nn, emb, b.M,
-                           (const int32_t *)nullptr, 0, b.mu, ctl, b.partial);
-      hipLaunchKernelGGL(k_energy_sum, dim3(1), dim3(64), 0, st, b.partial,
-                         kEnergyBlocks, ctl);
-      if (!first && g.link)  // the cut of the input graph, links aside
+        cut0[l] = ed0;
+      else if (g.link)  // the cut of the input graph, links aside
         hipLaunchKernelGGL(k_cut_e0, dim3(1024), dim3(256), 0, st, n, adj0,
-                           b.M, ctl);
-      else if (!first)
+                           b.M, l, ctl);
+      else
         hipLaunchKernelGGL(k_weight_sum, dim3(256), dim3(256), 0, st, nn, adj,
-                           ctl);
-      if ((rc = read_ctl(ctl, h, st))) return rc;
-      if (h->err) return status_from_err(h->err);
-      const int64_t cut2 = first ? (int64_t)ed0 : h->cut_w2;
-      const double cut = (double)(cut2 / 2);
-      const double reg = lambda * cut;
-      g.energy[l] = h->fid_total + reg;
+                           l, ctl);
     }
   }
   if (tail_level >= 0) {
     // the tail's own readback comes after its last kernel
-    return run_tail(g, b, emb, adj, cur, nn, ed, tail_level, tail_round,
+    return run_tail(g, b, emb, cut0, adj, cur, nn, ed, tail_level, tail_round,
                     max_rounds, ctl, h, st);
   }
   if ((rc = read_ctl(ctl, h, st))) return rc;
   if (h->err) return status_from_err(h->err);
+  fill_energy(g, h, cut0);
   return 0;
 }
 

@@ -204,8 +204,7 @@ __global__ void k_ctl_init(Ctl *ctl) {
     ctl->n_cbig = 0;
     ctl->n_tiles = 0;
     ctl->tail_level = -1;
-    ctl->cut_w2 = 0;
-    ctl->fid_total = 0.0;
+    for (int l = 0; l < 16; ++l) ctl->tail_cut2[l] = 0;
     ctl->maxabs_x_bits = 0;
     ctl->Fx = 0;
     ctl->n_iso = 0;
