@@ -1,7 +1,6 @@
 // ezsp_dev.h -- device-side building blocks shared by the HIP kernels of the
 // EZ-SP partition library (gfx950, wave64): the device control block, wave
-// and block scans, a device-wide scan driven by functors, and an LSD radix
-// sort of 64-bit keys with 32-bit payloads.
+// and block scans, and a device-wide scan driven by functors.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -347,15 +346,5 @@ struct ScanArray {
     if (i <= len()) out[i] = excl;
   }
 };
-
-// --- LSD radix sort of (uint64 key, uint32 value) -------------------------
-constexpr int kSortNT = 256;
-constexpr int kSortItems = 16;
-constexpr int kSortTile = kSortNT * kSortItems;
-constexpr int kSortBins = 256;
-
-inline int32_t sort_blocks(int64_t n) {
-  return (int32_t)((n + kSortTile - 1) / kSortTile);
-}
 
 }  // namespace ezsp

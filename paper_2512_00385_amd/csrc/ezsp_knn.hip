@@ -128,24 +128,16 @@ __global__ __launch_bounds__(256) void k_bbox(const float *xyz, int32_t n,
   }
 }
 
-// The box from its stripes, one wave: bbox_enc = min / max over them.
-__global__ __launch_bounds__(64) void k_bbox_fold(Ctl *ctl) {
-  const int lane = threadIdx.x;
-#pragma unroll
-  for (int a = 0; a < 6; ++a) {
-    int32_t v = lane < kStripes ? ctl->bbox_s[a][lane].v
-                                : f2ord(a < 3 ? INFINITY : -INFINITY);
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-      const int32_t o = __shfl_xor(v, off, kWave);
-      v = a < 3 ? min(v, o) : max(v, o);
-    }
-    if (lane == 0) ctl->bbox_enc[a] = v;
-  }
+// Bits per axis of the Morton codes.  The order only has to keep neighbours
+// close, so that fewer points need fewer bits: a quarter of the points of a
+// scene lie twice as far apart.  13 bits beat 12, 14 and 16 at 3M and 10M
+// points (10 bits leave dozens of points a voxel near a sensor: kNN 4.1
+// instead of 2.5 ms at 3M); 9 and 11 bits sort in three passes at the sizes
+// where a pass is launches and latency.
+constexpr int kMortonBits = 13;
+inline int morton_bits(int32_t n) {
+  return n <= (1 << 16) ? 9 : (n <= (1 << 19) ? 11 : kMortonBits);
 }
-
-constexpr int kMortonBits = 13;  // per axis
-constexpr float kMortonMax = (float)((1 << kMortonBits) - 1);
 
 // 16 bits -> every third bit of 48 (only the low kMortonBits are set).
 __device__ __forceinline__ uint64_t spread3(uint32_t v) {
@@ -161,32 +153,40 @@ __device__ __forceinline__ uint64_t spread3(uint32_t v) {
 // into the key's low kPackBits bits below the code, so that a key-only sort
 // of the code bits carries it.
 constexpr int kPackBits = 25;
+constexpr int kMortonPer = 4;  // points a thread: fewer blocks fold the box
 __global__ __launch_bounds__(256) void k_morton(const float *xyz, int32_t n,
-                                                const Ctl *ctl, uint64_t *keys,
+                                                int bits, const Ctl *ctl,
+                                                uint64_t *keys,
                                                 uint32_t *vals) {
-  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  __shared__ int32_t box[6];
+  fold_box(ctl, box);
   float lo[3], ext = 0.0f;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    lo[a] = ord2f(ctl->bbox_enc[a]);
-    ext = fmaxf(ext, ord2f(ctl->bbox_enc[3 + a]) - lo[a]);
+    lo[a] = ord2f(box[a]);
+    ext = fmaxf(ext, ord2f(box[3 + a]) - lo[a]);
   }
-  const float scale = (ext > 0.0f) ? kMortonMax / ext : 0.0f;
-  uint32_t q[3];
+  const float most = (float)((1 << bits) - 1);
+  const float scale = (ext > 0.0f) ? most / ext : 0.0f;
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    float t = (xyz[3 * (int64_t)i + a] - lo[a]) * scale;
-    t = fminf(fmaxf(t, 0.0f), kMortonMax);  // NaN maps to 0
-    q[a] = (uint32_t)t;
-  }
-  const uint64_t code =
-      spread3(q[0]) | (spread3(q[1]) << 1) | (spread3(q[2]) << 2);
-  if (vals) {
-    keys[i] = code;
-    vals[i] = (uint32_t)i;
-  } else {
-    keys[i] = (code << kPackBits) | (uint64_t)i;
+  for (int j = 0; j < kMortonPer; ++j) {
+    const int32_t i = (blockIdx.x * kMortonPer + j) * 256 + threadIdx.x;
+    if (i >= n) return;
+    uint32_t q[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      float t = (xyz[3 * (int64_t)i + a] - lo[a]) * scale;
+      t = fminf(fmaxf(t, 0.0f), most);  // NaN maps to 0
+      q[a] = (uint32_t)t;
+    }
+    const uint64_t code =
+        spread3(q[0]) | (spread3(q[1]) << 1) | (spread3(q[2]) << 2);
+    if (vals) {
+      keys[i] = code;
+      vals[i] = (uint32_t)i;
+    } else {
+      keys[i] = (code << kPackBits) | (uint64_t)i;
+    }
   }
 }
 
@@ -689,8 +689,10 @@ void knn_reserve(Arena &a, int32_t n, int32_t k, KnnWork *w) {
   w->nbr_int = a.take<int32_t>((size_t)n * pad4(k));
   w->keys = a.take<uint64_t>(n);
   w->keys2 = a.take<uint64_t>(n);
-  w->vals = a.take<uint32_t>(n);
-  w->vals2 = a.take<uint32_t>(n);
+  if (n > (1 << kPackBits)) {  // smaller n: the index rides in the key
+    w->vals = a.take<uint32_t>(n);
+    w->vals2 = a.take<uint32_t>(n);
+  }
   w->pts = a.take<float4>(pad_bucket(n));
   w->kth = a.take<uint64_t>(n);
   w->blo = a.take<float4>(t.total);
@@ -714,19 +716,20 @@ static hipError_t knn_impl(const float *xyz, int32_t n, int32_t k, Ctl *ctl,
   const int gb = (n + nt - 1) / nt;
   hipLaunchKernelGGL(k_bbox, dim3(min(gb, 256)), dim3(nt), 0, st, xyz, n,
                      ctl);
-  hipLaunchKernelGGL(k_bbox_fold, dim3(1), dim3(64), 0, st, ctl);
   // the index packed under the code when it fits in 64 bits: the sort then
   // moves 8 bytes a key instead of 12
   const bool pack = n <= (1 << kPackBits);
   static_assert(3 * kMortonBits + kPackBits <= 64, "code and index in a key");
-  hipLaunchKernelGGL(k_morton, dim3(gb), dim3(nt), 0, st, xyz, n, ctl, s.keys,
+  const int bits = morton_bits(n);
+  hipLaunchKernelGGL(k_morton, dim3((gb + kMortonPer - 1) / kMortonPer),
+                     dim3(nt), 0, st, xyz, n, bits, ctl, s.keys,
                      pack ? (uint32_t *)nullptr : s.vals);
   prof_begin("morton_sort", st);
   const bool alt =
-      pack ? radix_sort_keys(s.keys, s.keys2, n, kPackBits, 3 * kMortonBits,
+      pack ? radix_sort_keys(s.keys, s.keys2, n, kPackBits, 3 * bits,
                              s.hist, s.bsum, s.total, ctl, st)
            : radix_sort_pairs(s.keys, s.vals, s.keys2, s.vals2, n,
-                              3 * kMortonBits, s.hist, s.bsum, s.total, ctl,
+                              3 * bits, s.hist, s.bsum, s.total, ctl,
                               st);
   prof_end(st);
   const uint32_t *order = pack ? nullptr : (alt ? s.vals2 : s.vals);

@@ -1,6 +1,7 @@
 // ezsp_prims.hip -- device-wide scan tail, LSD radix sort, control block and
 // fixed-point shift kernels, and the host helpers shared by the launchers.
 #include <stdarg.h>
+#include <algorithm>
 #include <mutex>
 #include <string>
 #include <unordered_map>
@@ -46,138 +47,259 @@ __global__ __launch_bounds__(1024) void k_scan_bsums(int32_t *bsum, int32_t nb,
 }
 
 // ---------------------------------------------------------------------------
-// LSD radix sort, 8-bit digits.  Tile of kSortTile keys per block; inside a
-// tile, key j*256 + t is handled by thread t at step j, so (step, thread)
-// order is the input order and the per-step ranking keeps the sort stable.
+// LSD radix sort in tiles of keys, a histogram and a scatter a pass.  Inside
+// a tile every wave takes a contiguous share in steps of 64 keys, so (wave,
+// step, lane) order is the input order and the ranking is stable.
+//
+// A wave ranks its keys on its own: a step's lanes of equal digit find each
+// other by ballots and take their ranks from the wave's own LDS counters, so
+// the block meets only twice a tile (a common counter met twice every step).
+//
+// Digits: a pass costs launches and latencies more than bytes, so digits are
+// as wide as LDS counters allow, and equal in width.  Inputs of at most 2^16
+// keys take digits of up to 9 bits in tiles of 1024 (enough blocks), and the
+// scatter sums the tiles' histograms itself (at most 64 of them) instead of
+// a scan in between; up to 2^19 keys 11 bits, up to 2^21 10 bits, then 8 (a
+// tile's 4096 keys leave four a digit at 10 bits and the writes scatter: 39
+// bits of 3M keys 202 us in four passes, 190 in five; of 1M 10 us less in
+// four).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kSortNT) void k_rs_hist(const uint64_t *keys,
-                                                     int32_t n, int shift,
-                                                     int32_t *hist, int32_t nb) {
-  __shared__ int32_t h[kSortBins];
-  for (int d = threadIdx.x; d < kSortBins; d += kSortNT) h[d] = 0;
-  __syncthreads();
-  const int32_t base = blockIdx.x * kSortTile;
-#pragma unroll 4
-  for (int j = 0; j < kSortItems; ++j) {
-    int32_t i = base + j * kSortNT + threadIdx.x;
-    if (i < n) atomicAdd(&h[(keys[i] >> shift) & (kSortBins - 1)], 1);
-  }
-  __syncthreads();
-  for (int d = threadIdx.x; d < kSortBins; d += kSortNT)
-    hist[d * nb + blockIdx.x] = h[d];
+constexpr int kSmallNT = 256, kSmallItems = 4, kSmallBits = 9;
+constexpr int kMidBits = 11, kBigBits = 10, kHugeBits = 8;
+constexpr int kTileNT = 512, kTileItems = 8;
+constexpr int kSmallTile = kSmallNT * kSmallItems;
+constexpr int kSortTile = kTileNT * kTileItems;
+constexpr int32_t kSmallMax = 1 << 16, kMidMax = 1 << 19, kBigMax = 1 << 21;
+static_assert(kSmallMax / kSmallTile <= 64, "tiles a scatter block sums");
+
+inline int32_t tiles_of(int64_t n, int tile) {
+  return (int32_t)((n + tile - 1) / tile);
 }
 
-// The scatter takes a tile with twice the histogram's threads, half the
-// steps: fewer barriers for the same tile.
-constexpr int kScatNT = 2 * kSortNT;
-constexpr int kScatItems = kSortTile / kScatNT;
+// tile_major: hist[tile][digit], for a scatter that sums the tiles itself;
+// else hist[digit][tile], for a scan.
+template <int DB, int NT, int ITEMS>
+__global__ __launch_bounds__(NT) void k_rs_hist(
+    const uint64_t *__restrict__ keys, int32_t n, int shift, int db,
+    int32_t *__restrict__ hist, int32_t nb, bool tile_major) {
+  __shared__ int32_t h[1 << DB];
+  const int bins = 1 << db;
+  for (int d = threadIdx.x; d < bins; d += NT) h[d] = 0;
+  const int32_t base = blockIdx.x * (NT * ITEMS);
+  uint64_t kt[ITEMS];
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j)
+    kt[j] = keys[min(base + j * NT + (int32_t)threadIdx.x, n - 1)];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j)
+    if (base + j * NT + (int32_t)threadIdx.x < n)
+      atomicAdd(&h[(int)(kt[j] >> shift) & (bins - 1)], 1);
+  __syncthreads();
+  for (int d = threadIdx.x; d < bins; d += NT)
+    hist[tile_major ? (int32_t)blockIdx.x * bins + d
+                    : d * nb + (int32_t)blockIdx.x] = h[d];
+}
 
 // VALS: keys carry 32-bit values; otherwise the keys alone (a value packed
-// into bits the sort does not look at).
-template <bool VALS>
-__global__ __launch_bounds__(kScatNT) void k_rs_scatter(
+// into bits the sort does not look at).  SUM: hist holds the tiles' counts
+// (tile major), and the block sums them; else their scan (digit major).
+template <bool VALS, int DB, int NT, int ITEMS, bool SUM>
+__global__ __launch_bounds__(NT) void k_rs_scatter(
     const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int32_t n,
-    int shift, const int32_t *__restrict__ offs, int32_t nb, Ctl *ctl) {
-  constexpr int kW = kScatNT / kWave;
-  static_assert(kSortBins <= kScatNT, "one digit per thread in the prefix");
-  __shared__ int32_t run[kSortBins];
-  // per step: the waves' counts per digit, and the positions they turn
-  // into (kept apart so that the counts can be reset while the positions
-  // are read: two barriers a step)
-  __shared__ int32_t cnt[kW][kSortBins];
-  __shared__ int32_t pos0[kW][kSortBins];
+    int shift, int db, const int32_t *__restrict__ hist, int32_t nb,
+    Ctl *ctl) {
+  constexpr int kW = NT / kWave;
+  constexpr int kPer = (1 << DB) > NT ? (1 << DB) / NT : 1;
+  // a digit's first position in this tile, and the waves' counts of it,
+  // which then turn into the waves' first positions
+  __shared__ int32_t run[1 << DB];
+  __shared__ int32_t cnt[kW][1 << DB];
+  __shared__ int32_t wsum[kW];
+  const int bins = 1 << db;
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = threadIdx.x / kWave;
-  if (threadIdx.x < kSortBins) {
-    run[threadIdx.x] = offs[threadIdx.x * nb + blockIdx.x];
+  // the thread's keys of the whole tile, loaded before anything is waited for
+  const int32_t base =
+      blockIdx.x * (NT * ITEMS) + wid * (ITEMS * kWave) + lane;
+  uint64_t kt[ITEMS];
+  uint32_t vt[ITEMS];
 #pragma unroll
-    for (int w = 0; w < kW; ++w) cnt[w][threadIdx.x] = 0;
-  }
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-  const int32_t base = blockIdx.x * kSortTile;
-  // the thread's keys and values of the whole tile, loaded before the first
-  // step (clamped indices, no branch): the steps then wait on LDS only
-  uint64_t kt[kScatItems];
-  uint32_t vt[kScatItems];
-#pragma unroll
-  for (int j = 0; j < kScatItems; ++j) {
-    const int32_t i = min(base + j * kScatNT + (int32_t)threadIdx.x, n - 1);
+  for (int j = 0; j < ITEMS; ++j) {
+    const int32_t i = min(base + j * kWave, n - 1);
     kt[j] = kin[i];
     vt[j] = VALS ? vin[i] : 0u;
   }
-  __syncthreads();
+  for (int d = threadIdx.x; d < bins; d += NT)
 #pragma unroll
-  for (int j = 0; j < kScatItems; ++j) {
-    const int32_t i = base + j * kScatNT + threadIdx.x;
-    const bool valid = i < n;
-    const uint64_t key = valid ? kt[j] : 0ull;
-    const uint32_t val = valid ? vt[j] : 0u;
-    const int dig = (int)((key >> shift) & (kSortBins - 1));
+    for (int w = 0; w < kW; ++w) cnt[w][d] = 0;
+  if (SUM) {
+    int32_t before[kPer], total[kPer], sum = 0;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) before[e] = total[e] = 0;
+    const int d0 = (int)threadIdx.x * kPer;
+    if (d0 < bins) {
+#pragma unroll 8
+      for (int32_t t = 0; t < nb; ++t)
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+          const int32_t c = d0 + e < bins ? hist[t * bins + d0 + e] : 0;
+          total[e] += c;
+          before[e] += t < (int32_t)blockIdx.x ? c : 0;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) sum += total[e];
+    int32_t all;
+    int32_t at = block_excl_scan<NT>(sum, wsum, &all);
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      if (d0 + e < bins) run[d0 + e] = at + before[e];
+      at += total[e];
+    }
+  } else {
+    for (int d = threadIdx.x; d < bins; d += NT)
+      run[d] = hist[d * nb + (int32_t)blockIdx.x];
+  }
+  __syncthreads();
+  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+  volatile int32_t *mine = cnt[wid];
+  int32_t rank[ITEMS];
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    const bool valid = base + j * kWave < n;
+    const int dig = (int)(kt[j] >> shift) & (bins - 1);
     uint64_t peers = __ballot(valid);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int bit = (dig >> b) & 1;
-      const uint64_t bal = __ballot(bit);
-      peers &= bit ? bal : ~bal;
+    for (int b = 0; b < DB; ++b) {
+      if (b < db) {
+        const int bit = (dig >> b) & 1;
+        const uint64_t bal = __ballot(bit);
+        peers &= bit ? bal : ~bal;
+      }
     }
-    const int rank = __popcll(peers & lt_mask);
-    if (valid && rank == 0) cnt[wid][dig] = __popcll(peers);
-    __syncthreads();
-    if (threadIdx.x < kSortBins) {
-      const int d = threadIdx.x;
-      int32_t p = run[d];
+    const int32_t prev = mine[dig];
+    const int r = __popcll(peers & lt_mask);
+    rank[j] = prev + r;
+    if (valid && r == 0) mine[dig] = prev + (int32_t)__popcll(peers);
+    __builtin_amdgcn_wave_barrier();  // the next step reads these counts
+  }
+  __syncthreads();
+  for (int d = threadIdx.x; d < bins; d += NT) {
+    int32_t p = run[d];
 #pragma unroll
-      for (int w = 0; w < kW; ++w) {
-        const int32_t c = cnt[w][d];
-        cnt[w][d] = 0;
-        pos0[w][d] = p;
-        p += c;
-      }
-      run[d] = p;
+    for (int w = 0; w < kW; ++w) {
+      const int32_t c = cnt[w][d];
+      cnt[w][d] = p;
+      p += c;
     }
-    __syncthreads();
-    if (valid) {
-      const int32_t pos = pos0[wid][dig] + rank;
-      if ((uint32_t)pos < (uint32_t)n) {
-        kout[pos] = key;
-        if (VALS) vout[pos] = val;
-      } else {
-        raise_err(ctl, kErrInternal);
-      }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < ITEMS; ++j) {
+    if (base + j * kWave >= n) break;
+    const int dig = (int)(kt[j] >> shift) & (bins - 1);
+    const int32_t pos = cnt[wid][dig] + rank[j];
+    if ((uint32_t)pos < (uint32_t)n) {
+      kout[pos] = kt[j];
+      if (VALS) vout[pos] = vt[j];
+    } else {
+      raise_err(ctl, kErrInternal);
     }
   }
 }
 
+// Histogram words for any n up to the given one (so that a workspace sized
+// for more points also serves fewer).
 size_t radix_hist_ints(int32_t n) {
-  return (size_t)kSortBins * (size_t)sort_blocks(n);
+  const size_t small =
+      ((size_t)1 << kSmallBits) * tiles_of(n < kSmallMax ? n : kSmallMax,
+                                           kSmallTile);
+  const size_t mid = ((size_t)1 << kMidBits) *
+                     tiles_of(n < kMidMax ? n : kMidMax, kSortTile);
+  const size_t big = ((size_t)1 << kBigBits) *
+                     tiles_of(n < kBigMax ? n : kBigMax, kSortTile);
+  const size_t huge = ((size_t)1 << kHugeBits) * tiles_of(n, kSortTile);
+  return std::max(std::max(small, mid), std::max(big, huge));
 }
+
+namespace {
+
+struct SortBufs {
+  uint64_t *kin, *kout;
+  uint32_t *vin, *vout;
+  int32_t *hist, *bsum, *total;
+};
+
+template <bool VALS, int DB, int NT, int ITEMS, bool SUM>
+void sort_pass(const SortBufs &b, int32_t n, int shift, int db, Ctl *ctl,
+               hipStream_t st) {
+  const int32_t nb = tiles_of(n, NT * ITEMS);
+  hipLaunchKernelGGL((k_rs_hist<DB, NT, ITEMS>), dim3(nb), dim3(NT), 0, st,
+                     b.kin, n, shift, db, b.hist, nb, SUM);
+  if (!SUM) {
+    const int32_t nh = nb << db;
+    device_scan(ScanArray{b.hist, b.hist, nh, nullptr}, nh, b.bsum, b.total,
+                st);
+  }
+  hipLaunchKernelGGL((k_rs_scatter<VALS, DB, NT, ITEMS, SUM>), dim3(nb),
+                     dim3(NT), 0, st, b.kin, b.vin, b.kout, b.vout, n, shift,
+                     db, b.hist, nb, ctl);
+}
+
+template <bool VALS>
+bool sort_run(SortBufs b, int32_t n, int shift0, int nbits, Ctl *ctl,
+              hipStream_t st) {
+  if (n <= 1 || nbits <= 0) return false;
+  const int most = n <= kSmallMax ? kSmallBits
+                   : n <= kMidMax ? kMidBits
+                   : n <= kBigMax ? kBigBits
+                                  : kHugeBits;
+  const int passes = (nbits + most - 1) / most;
+  bool flip = false;
+  int shift = shift0;
+  for (int q = 0; q < passes; ++q) {
+    // the bits left over the passes left, so digits differ by a bit at most
+    const int left = shift0 + nbits - shift;
+    const int db = (left + passes - q - 1) / (passes - q);
+    if (n <= kSmallMax)
+      sort_pass<VALS, kSmallBits, kSmallNT, kSmallItems, true>(b, n, shift, db,
+                                                               ctl, st);
+    else if (n <= kMidMax)
+      sort_pass<VALS, kMidBits, kTileNT, kTileItems, false>(b, n, shift, db,
+                                                            ctl, st);
+    else if (n <= kBigMax)
+      sort_pass<VALS, kBigBits, kTileNT, kTileItems, false>(b, n, shift, db,
+                                                            ctl, st);
+    else
+      sort_pass<VALS, kHugeBits, kTileNT, kTileItems, false>(b, n, shift, db,
+                                                             ctl, st);
+    std::swap(b.kin, b.kout);
+    std::swap(b.vin, b.vout);
+    shift += db;
+    flip = !flip;
+  }
+  return flip;
+}
+
+}  // namespace
 
 bool radix_sort_pairs(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt,
                       uint32_t *vals_alt, int32_t n, int nbits,
                       int32_t *hist, int32_t *bsum, int32_t *total, Ctl *ctl,
                       hipStream_t st) {
-  if (n <= 1) return false;
-  const int32_t nb = sort_blocks(n);
-  uint64_t *kin = keys, *kout = keys_alt;
-  uint32_t *vin = vals, *vout = vals_alt;
-  bool flip = false;
-  for (int shift = 0; shift < nbits; shift += 8) {
-    hipLaunchKernelGGL(k_rs_hist, dim3(nb), dim3(kSortNT), 0, st, kin, n,
-                       shift, hist, nb);
-    const int32_t nh = kSortBins * nb;
-    device_scan(ScanArray{hist, hist, nh, nullptr}, nh, bsum, total, st);
-    hipLaunchKernelGGL(k_rs_scatter<true>, dim3(nb), dim3(kScatNT), 0, st,
-                       kin, vin, kout, vout, n, shift, hist, nb, ctl);
-    uint64_t *tk = kin;
-    kin = kout;
-    kout = tk;
-    uint32_t *tv = vin;
-    vin = vout;
-    vout = tv;
-    flip = !flip;
-  }
-  return flip;
+  return sort_run<true>(
+      SortBufs{keys, keys_alt, vals, vals_alt, hist, bsum, total}, n, 0, nbits,
+      ctl, st);
+}
+
+bool radix_sort_keys(uint64_t *keys, uint64_t *keys_alt, int32_t n,
+                     int shift0, int nbits, int32_t *hist, int32_t *bsum,
+                     int32_t *total, Ctl *ctl, hipStream_t st) {
+  return sort_run<false>(
+      SortBufs{keys, keys_alt, nullptr, nullptr, hist, bsum, total}, n, shift0,
+      nbits, ctl, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -271,29 +393,6 @@ __global__ void k_fixshift(Ctl *ctl, int32_t n) {
   const int F = fixshift_rule(__uint_as_float(bits), n);
   ctl->F = F;
   if (F < 16) raise_err(ctl, kErrRange);
-}
-
-bool radix_sort_keys(uint64_t *keys, uint64_t *keys_alt, int32_t n,
-                     int shift0, int nbits, int32_t *hist, int32_t *bsum,
-                     int32_t *total, Ctl *ctl, hipStream_t st) {
-  if (n <= 1) return false;
-  const int32_t nb = sort_blocks(n);
-  uint64_t *kin = keys, *kout = keys_alt;
-  bool flip = false;
-  for (int shift = shift0; shift < shift0 + nbits; shift += 8) {
-    hipLaunchKernelGGL(k_rs_hist, dim3(nb), dim3(kSortNT), 0, st, kin, n,
-                       shift, hist, nb);
-    const int32_t nh = kSortBins * nb;
-    device_scan(ScanArray{hist, hist, nh, nullptr}, nh, bsum, total, st);
-    hipLaunchKernelGGL(k_rs_scatter<false>, dim3(nb), dim3(kScatNT), 0, st,
-                       kin, (const uint32_t *)nullptr, kout, (uint32_t *)nullptr,
-                       n, shift, hist, nb, ctl);
-    uint64_t *tk = kin;
-    kin = kout;
-    kout = tk;
-    flip = !flip;
-  }
-  return flip;
 }
 
 // ---------------------------------------------------------------------------
