@@ -501,9 +501,19 @@ __device__ __forceinline__ void set_level_bits(uint64_t &mlo, uint64_t &mhi,
 // that lane's current k-th distance.  ST: also count, per wave, the
 // buckets it scans (its own included) and the inner nodes it enters
 // (st_scan, st_node; the walk statistics, a separate instantiation).
+// Waves per SIMD: eight up to K = 16 (there at the price of 24 registers
+// spilled, still 3 % faster than seven waves with none), then as many as the
+// list of K keys (2 K registers) leaves room for without spilling: holding
+// the longer lists to 64 registers spilled hundreds at K = 32 and 64.
+// 500,000 points of a street tile, whole kNN: k = 20 5.5 -> 1.5 ms, k = 32
+// 5.6 -> 1.9 ms, k = 64 108 -> 11.7 ms.
+constexpr int query_waves(int K) {
+  return K <= 16 ? 8 : (K <= 24 ? 5 : (K <= 32 ? 4 : 2));
+}
 template <int K, bool ST = false>
 __global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(8, 8))) void k_knn_query(
+__attribute__((amdgpu_waves_per_eu(query_waves(K), query_waves(K)))) void
+k_knn_query(
     const float4 *__restrict__ pts, const int32_t *__restrict__ inv,
     int32_t n, const float4 *__restrict__ blo, const float4 *__restrict__ bhi,
     Tree tree, int32_t k, int32_t *__restrict__ nbr_int,
@@ -673,10 +683,259 @@ __attribute__((amdgpu_waves_per_eu(8, 8))) void k_knn_query(
 }
 
 // ---------------------------------------------------------------------------
+// The same query with a wavefront per bucket: 16 queries, each held by the
+// four DPP rows alike (the same list in every row).  A row scores a quarter of
+// a bucket's candidates, and the tests of a node's eight children run at once,
+// two a row; so a wave has a quarter of the wide walk's queries, and no step
+// waits for one box at a time.  It issues about twice the instructions a
+// query, but its waves are four times as many and end much sooner: while the
+// wide walk's waves do not fill the chip, the time is that of its slowest
+// wave (64 consecutive points across a jump of the Morton curve).
+// ---------------------------------------------------------------------------
+template <int K, int S, int R>
+struct NarrowInsert {
+  // candidate S of row R, the same point for all queries, from scalars
+  __device__ __forceinline__ static void run(uint64_t takers, const float4 &q,
+                                             const float4 &p,
+                                             uint64_t (&key)[K]) {
+    if ((takers >> (16 * R)) & 0xffffu) {
+      constexpr int src = 16 * R + S;
+      const auto lane_f = [](float v) {
+        return __int_as_float(
+            __builtin_amdgcn_readlane(__float_as_int(v), src));
+      };
+      const float dx = lane_f(q.x) - p.x;
+      const float dy = lane_f(q.y) - p.y;
+      const float dz = lane_f(q.z) - p.z;
+      const int32_t qo =
+          __builtin_amdgcn_readlane(__float_as_int(q.w), src);
+      const uint64_t nk =
+          cand_key(fmaf(dz, dz, fmaf(dy, dy, dx * dx)), qo);
+      if (nk < key[K - 1]) topk_insert<K>(key, nk);
+    }
+    NarrowInsert<K, S, R + 1>::run(takers, q, p, key);
+  }
+};
+template <int K, int S>
+struct NarrowInsert<K, S, 4> {
+  __device__ __forceinline__ static void run(uint64_t, const float4 &,
+                                             const float4 &,
+                                             uint64_t (&)[K]) {}
+};
+
+// Scores candidate S of every row's quarter; the few that some query takes
+// are inserted in all rows.
+template <int K, int S>
+struct NarrowStep {
+  __device__ __forceinline__ static void run(const float4 &q, const float4 &p,
+                                             bool act, uint64_t (&key)[K]) {
+    const uint64_t nk = bucket_key<S, false>(q, p.x, p.y, p.z, -1);
+    const uint64_t takers = __ballot(act && nk < key[K - 1]);
+    if (takers) NarrowInsert<K, S, 0>::run(takers, q, p, key);
+    NarrowStep<K, S + 1>::run(q, p, act, key);
+  }
+};
+template <int K>
+struct NarrowStep<K, 4> {
+  __device__ __forceinline__ static void run(const float4 &, const float4 &,
+                                             bool, uint64_t (&)[K]) {}
+};
+
+// Bit c: some query's box distance (child row in a, row + 4 in b) does not
+// exceed its k-th distance.
+__device__ __forceinline__ uint32_t narrow_need(float a, float b,
+                                                uint32_t kth, bool act) {
+  const uint64_t m0 = __ballot(act && __float_as_uint(a) <= kth);
+  const uint64_t m1 = __ballot(act && __float_as_uint(b) <= kth);
+  uint32_t m = 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    m |= ((m0 >> (16 * r)) & 0xffffu) ? 1u << r : 0u;
+    m |= ((m1 >> (16 * r)) & 0xffffu) ? 16u << r : 0u;
+  }
+  return m;
+}
+
+constexpr int narrow_waves(int K) { return K <= 16 ? 7 : 5; }
+template <int K>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(narrow_waves(K)))) void k_knn_narrow(
+    const float4 *__restrict__ pts, const int32_t *__restrict__ inv,
+    int32_t n, const float4 *__restrict__ blo, const float4 *__restrict__ bhi,
+    Tree tree, int32_t k, int32_t *__restrict__ nbr_int,
+    int32_t *__restrict__ nbr_out, float *__restrict__ d2_out,
+    uint64_t *__restrict__ kth_out, const float4 *__restrict__ emb,
+    int32_t d4, float4 *__restrict__ emb_out, Ctl *ctl) {
+  const int32_t b0 = __builtin_amdgcn_readfirstlane(
+      xcd_block() * (256 / kWave) + (int32_t)(threadIdx.x / kWave));
+  const int32_t nb0 = tree.cnt[0];
+  if (b0 >= nb0) return;  // whole waves only
+  const int lane = threadIdx.x & (kWave - 1);
+  const int lane16 = lane & (kBucket - 1);
+  const int row = lane / kBucket;
+  // a row loads a bucket rotated by its quarter: its candidates lie in its
+  // lanes 0..3
+  const int turned = (lane16 + 4 * row) & (kBucket - 1);
+  const int32_t i = b0 * kBucket + lane16;
+  const bool act = i < n;
+  const float4 own = pts[i];  // padded to whole buckets
+  // the buckets to scan next, loaded ahead (scalars: which of them there are,
+  // from the lowest bit); first the own bucket's two Morton neighbours
+  float4 q0 = pts[max(b0 - 1, 0) * kBucket + turned];
+  float4 q1 = pts[min(b0 + 1, nb0 - 1) * kBucket + turned];
+  float4 q2, q3;
+  if (b0 == 0) q0 = q1;
+  int todo = (b0 > 0 ? 1 : 0) + (b0 + 1 < nb0 ? 1 : 0);
+  const float4 p = act ? own : make_float4(0.f, 0.f, 0.f, 0.f);
+  const int32_t me = act ? __float_as_int(p.w) : -1;
+  float4 erow = make_float4(0.f, 0.f, 0.f, 0.f);
+  const bool has_row = emb && act && row < d4;  // d4 <= 4: a vector a row
+  if (has_row) erow = emb[(int64_t)me * d4 + row];
+  uint64_t key[K];
+#pragma unroll
+  for (int t = 0; t < K; ++t) key[t] = kEmpty;
+  BucketStep<K, 0, true>::run(own, p.x, p.y, p.z, me, key);
+  if (emb) {
+    uint32_t m = 0;
+    bool bad = false;
+    if (has_row) {
+      emb_out[(int64_t)i * d4 + row] = erow;
+      const float v[4] = {erow.x, erow.y, erow.z, erow.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (!isfinite(v[j])) bad = true;
+        else m = max(m, __float_as_uint(fabsf(v[j])));
+      }
+    }
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1)
+      m = max(m, (uint32_t)__shfl_xor((int)m, off, kWave));
+    const bool any_bad = __ballot(bad) != 0;
+    if (lane == 0) {
+      stripe_max(ctl->maxabs_s, (int32_t)m);  // |e| bits < 2^31
+      if (any_bad) raise_err(ctl, kErrNonFinite);
+    }
+  }
+
+  // Depth-first walk as in k_knn_query (pending children of every level of
+  // the path as bits), but a node's children are all tested per query when
+  // it is entered, and a node taken later is entered at once: the test of its
+  // own children with the k-th distances of then is as cheap as a test of
+  // its box.  Leaves are scanned where their parent is entered, four loaded
+  // ahead, and re-tested with the distances kept from the entry.
+  uint64_t mlo = 0, mhi = 0;
+  int32_t node = 0, first = 0;
+  int l = tree.top;   // the level of `node`
+  bool down = false;  // the root has been entered
+  float da = 0.0f, db = 0.0f;
+  uint32_t left = 0, m8 = 0, batch = 0;  // leaves of the node: not yet
+                                         // scanned, needed, loaded
+  for (;;) {
+    // the loaded buckets, in turn; each shortens the k-th distances the
+    // rest are tested with (batch is 0 for the two neighbours)
+#pragma unroll 1
+    while (todo > 0) {
+      const uint32_t bit = batch & (0u - batch);
+      if (bit == 0 || (m8 & bit)) {
+        NarrowStep<K, 0>::run(q0, p, act, key);
+        m8 = narrow_need(da, db, (uint32_t)(key[K - 1] >> 32), act) & left;
+      }
+      batch ^= bit;
+      left &= ~bit;
+      q0 = q1;
+      q1 = q2;
+      q2 = q3;
+      --todo;
+    }
+    m8 &= left;
+    if (m8 == 0) {  // the next node
+      if (!down) {
+        down = true;
+        if (tree.top == 0) break;
+      } else {
+        int t;
+        if (mlo != 0) {
+          t = __builtin_ctzll(mlo);
+          mlo &= mlo - 1;
+        } else {
+          // levels 8 and up (trees over more than 8^8 buckets only)
+          if (mhi == 0) break;
+          t = 64 + __builtin_ctzll(mhi);
+          mhi &= mhi - 1;
+        }
+        const int lt = t >> 3;
+        node = ((node >> (3 * (lt + 1 - l))) << 3) | (t & 7);
+        l = lt;
+      }
+      const int lc = l - 1;
+      first = node * kFan;
+      const int32_t nchild = min(kFan, tree.cnt[lc] - first);
+      const int32_t at = tree.off[lc] + first;
+      const int32_t j0 = at + min(row, nchild - 1);
+      const int32_t j1 = at + min(row + 4, nchild - 1);
+      da = box_d2(blo[j0], bhi[j0], p.x, p.y, p.z);
+      db = box_d2(blo[j1], bhi[j1], p.x, p.y, p.z);
+      left = (1u << nchild) - 1u;
+      m8 = narrow_need(da, db, (uint32_t)(key[K - 1] >> 32), act) & left;
+      if (lc > 0) {
+        set_level_bits(mlo, mhi, lc, m8);
+        m8 = 0;
+        continue;
+      }
+      // the own bucket and the two next to it are done
+#pragma unroll
+      for (int e = -1; e <= 1; ++e) {
+        const int32_t c = b0 + e - first;
+        if (c >= 0 && c < kFan) left &= ~(1u << c);
+      }
+      m8 &= left;
+    }
+    // up to four of the needed leaves, loaded together
+    uint32_t rest = m8;
+    todo = min((int)__popc(m8), 4);
+    batch = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t bit = rest & (0u - rest);
+      batch |= bit;
+      if (bit) {
+        const float4 q = pts[(first + __builtin_ctz(bit)) * kBucket + turned];
+        if (u == 0) q0 = q;
+        if (u == 1) q1 = q;
+        if (u == 2) q2 = q;
+        if (u == 3) q3 = q;
+      }
+      rest ^= bit;
+    }
+  }
+
+  if (!act) return;
+  const int32_t kp = pad4(k);
+#pragma unroll
+  for (int t = 0; t < K; ++t)
+    if (t == k - 1 && row == 0)
+      kth_out[i] = (uint32_t)key[t] < (uint32_t)n ? key[t] : kNoKey;
+#pragma unroll
+  for (int t = 0; t < K; ++t) {
+    if (t < k && (t & 3) == row) {
+      const bool has = (uint32_t)key[t] < (uint32_t)n;
+      const int32_t o = (int32_t)(uint32_t)key[t];
+      nbr_int[(int64_t)i * kp + t] = has ? inv[o] : -1;
+      if (nbr_out) nbr_out[(int64_t)me * k + t] = has ? o : -1;
+      if (d2_out)
+        d2_out[(int64_t)me * k + t] =
+            has ? __uint_as_float((uint32_t)(key[t] >> 32)) : INFINITY;
+    }
+  }
+  if (row == 0)
+    for (int32_t t = k; t < kp; ++t) nbr_int[(int64_t)i * kp + t] = -1;
+}
+
+// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 static int knn_template_k(int32_t k) {
-  static const int ks[] = {4, 8, 10, 16, 32, 64};
+  static const int ks[] = {4, 8, 10, 16, 24, 32, 64};
   for (int v : ks)
     if (k <= v) return v;
   return -1;
@@ -700,6 +959,17 @@ void knn_reserve(Arena &a, int32_t n, int32_t k, KnnWork *w) {
   w->hist = a.take<int32_t>(radix_hist_ints(n));
   w->bsum = a.take<int32_t>(scan_blocks(radix_hist_ints(n)) + 1);
   w->total = a.take<int32_t>(4);
+}
+
+// The largest input of the walk with a wave per bucket.  k = 10, whole kNN
+// in us, wide / narrow, room, street, aerial tile and sweep: 20,000 points
+// 161/104 229/164 253/168 185/142; 120,000 274/244 395/312 502/375 190/194;
+// 250,000 312/319 478/428 560/426 255/302; 500,000 392/462 488/536 642/522
+// 357/444.  Longer lists fill the chip sooner (their insertions are the
+// work): K = 24 ends at 2^15 points, 32 and 64 never gain.
+constexpr int kNarrowK = 24;
+constexpr int32_t narrow_max(int K) {
+  return K <= 16 ? 1 << 18 : (K <= kNarrowK ? 1 << 15 : 0);
 }
 
 // the largest level left to the single-block kernel
@@ -762,6 +1032,12 @@ static hipError_t knn_impl(const float *xyz, int32_t n, int32_t k, Ctl *ctl,
                          s.pts, w.inv, n, s.blo, s.bhi, tree, k, w.nbr_int,  \
                          nbr_out, d2_out, w.kth, n_waves, emb4, d / 4,       \
                          emb_out4, ctl, st_scan, st_node);                   \
+    else if (n <= narrow_max(KK))                                            \
+      hipLaunchKernelGGL(k_knn_narrow<(KK <= kNarrowK ? KK : kNarrowK)>,     \
+                         dim3(xcd_grid((tree.cnt[0] + 3) / 4)), dim3(nt), 0, \
+                         st, s.pts, w.inv, n, s.blo, s.bhi, tree, k,         \
+                         w.nbr_int, nbr_out, d2_out, w.kth, emb4, d / 4,     \
+                         emb_out4, ctl);                                     \
     else                                                                     \
       hipLaunchKernelGGL(k_knn_query<KK>, grid, dim3(nt), 0, st, s.pts,      \
                          w.inv, n, s.blo, s.bhi, tree, k, w.nbr_int,         \
@@ -773,6 +1049,7 @@ static hipError_t knn_impl(const float *xyz, int32_t n, int32_t k, Ctl *ctl,
     EZSP_KNN_CASE(8)
     EZSP_KNN_CASE(10)
     EZSP_KNN_CASE(16)
+    EZSP_KNN_CASE(24)
     EZSP_KNN_CASE(32)
     EZSP_KNN_CASE(64)
 #undef EZSP_KNN_CASE

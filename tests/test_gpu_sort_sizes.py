@@ -60,3 +60,20 @@ def test_workspaces_grow_with_n():
                   lambda n: lib.ezsp_purity_workspace_size(n, 9000, 500)):
         got = [query(n) for n in sizes if n > 0]
         assert got == sorted(got)
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 1025, 9000, 32_768, 32_769])
+@pytest.mark.parametrize("k", [3, 8, 9, 16, 17, 24, 25, 40])
+def test_neighbours_of_both_walks(n, k):
+    # few points to a wave and many: ties (a lattice), repeated points, lists
+    # longer than the cloud, a last bucket partly filled, far-off points
+    rng = np.random.default_rng(n + k)
+    xyz = rng.integers(0, 12, (n, 3)).astype(np.float32)
+    far = rng.random(n) < 0.05
+    xyz[far] = (rng.random((int(far.sum()), 3)) * 1000).astype(np.float32)
+    dense = rng.random(n) < 0.5
+    xyz[dense] += (rng.random((int(dense.sum()), 3)) * 0.3).astype(np.float32)
+    nbr, d2 = ezsp.knn(torch.from_numpy(xyz).cuda(), k, want_d2=True)
+    ref, rd2 = oracle.knn(xyz, k, "brute" if n <= 3000 else "kdtree")
+    assert np.array_equal(nbr.cpu().numpy(), ref)
+    assert np.array_equal(d2.cpu().numpy(), rd2)
