@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace ezsp {
 
@@ -142,22 +143,62 @@ __device__ __forceinline__ void raise_err(Ctl *ctl, uint32_t bits) {
 }
 
 // --- wave / block scans (wave64) ------------------------------------------
+// The scan steps of 32- and 64-bit integers go through DPP (row shifts, then
+// the rows' last lanes broadcast on), eight cycles each where a shuffle takes
+// an LDS round trip of a hundred.  Every lane of the wave must be active.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int32_t dpp_or_zero(int32_t v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS, class T>
+__device__ __forceinline__ T dpp_add(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return v + (T)dpp_or_zero<CTRL, ROWS>((int32_t)v);
+  } else {
+    const uint32_t lo =
+        (uint32_t)dpp_or_zero<CTRL, ROWS>((int32_t)(uint32_t)(uint64_t)v);
+    const uint32_t hi =
+        (uint32_t)dpp_or_zero<CTRL, ROWS>((int32_t)((uint64_t)v >> 32));
+    return v + (T)(((uint64_t)hi << 32) | lo);
+  }
+}
+
 template <class T>
 __device__ __forceinline__ T wave_incl_scan(T v) {
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    T t = __shfl_up(v, off, kWave);
-    if (lane >= off) v += t;
-  }
+  static_assert(std::is_integral<T>::value, "integers");
+  v = dpp_add<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
   return v;
 }
 
 template <class T>
+__device__ __forceinline__ T wave_last(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return (T)__builtin_amdgcn_readlane((int32_t)v, kWave - 1);
+  } else {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(
+        (int32_t)(uint32_t)(uint64_t)v, kWave - 1);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(
+        (int32_t)((uint64_t)v >> 32), kWave - 1);
+    return (T)(((uint64_t)hi << 32) | lo);
+  }
+}
+
+// Sum over the wave, in every lane.
+template <class T>
 __device__ __forceinline__ T wave_sum(T v) {
+  if constexpr (std::is_integral<T>::value) {
+    return wave_last(wave_incl_scan(v));
+  } else {
 #pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
+    for (int off = kWave / 2; off > 0; off >>= 1)
+      v += __shfl_xor(v, off, kWave);
+    return v;
+  }
 }
 
 // Exclusive scan over a block of NT threads; *total gets the block sum.

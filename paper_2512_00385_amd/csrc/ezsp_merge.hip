@@ -2465,11 +2465,52 @@ __device__ __forceinline__ double tail_gain(const double *__restrict__ mu,
   return cut - fit;
 }
 
+// Entries of the tail's tables name both ends (node ids are below 2^16):
+// row v above neighbour u, over the weight.  A pass over slots needs no
+// search for an entry's row then.
+__device__ __forceinline__ uint64_t tail_entry(int32_t v, int32_t u,
+                                               uint32_t w) {
+  return ((uint64_t)(((uint32_t)v << 16) | (uint32_t)u) << 32) | w;
+}
+__device__ __forceinline__ int32_t tail_v(uint64_t e) {
+  return (int32_t)(e >> 48);
+}
+__device__ __forceinline__ int32_t tail_u(uint64_t e) {
+  return (int32_t)((e >> 32) & 0xffffu);
+}
+
+// Block sum of v, in every thread.  Contains barriers; wsum may be used
+// again after them.
+__device__ __forceinline__ int32_t tail_sum(int32_t v, int32_t *wsum) {
+  v = wave_sum(v);
+  if ((threadIdx.x & (kWave - 1)) == 0) wsum[threadIdx.x / kWave] = v;
+  __syncthreads();
+  int32_t t = 0;
+#pragma unroll
+  for (int w = 0; w < kTailNT / kWave; ++w) t += wsum[w];
+  __syncthreads();
+  return t;
+}
+
+// Appends v of the lanes with `take` to an LDS list, in no particular order
+// (one atomic a wave).
+__device__ __forceinline__ void tail_append(bool take, int32_t v,
+                                            int32_t *list, int32_t *count) {
+  const uint64_t m = __ballot(take);
+  if (!m) return;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int first = __ffsll((unsigned long long)m) - 1;
+  int32_t at = 0;
+  if (lane == first) at = atomicAdd(count, (int32_t)__popcll(m));
+  at = __builtin_amdgcn_readlane(at, first);
+  if (take) list[at + __popcll(m & ((1ull << lane) - 1ull))] = v;
+}
+
 // Calls f(p, v, e) for every non-empty entry e of the rows whose flattened
 // positions pos[] spans (P positions in all): row v, table tb.  The entries
-// and rows of kTU positions per thread are loaded before any is used.
-template <int U = kTU, class Fn>
-__device__ __forceinline__ void tail_entries(const int32_t *pos, int32_t nn,
+// and rows of U positions per thread are loaded before any is used.
+template <int U, class Fn>
+__device__ __forceinline__ void tail_entries_u(const int32_t *pos, int32_t nn,
                                              int32_t P, const int32_t *s_ws,
                                              const uint64_t *tb, Fn &&f) {
   for (int32_t p0 = threadIdx.x; p0 < P; p0 += U * kTailNT) {
@@ -2489,6 +2530,18 @@ __device__ __forceinline__ void tail_entries(const int32_t *pos, int32_t nn,
   }
 }
 
+// Eight positions a thread only when there are that many: every search is
+// eleven LDS reads, also for positions past the end.
+template <class Fn>
+__device__ __forceinline__ void tail_entries(const int32_t *pos, int32_t nn,
+                                             int32_t P, const int32_t *s_ws,
+                                             const uint64_t *tb, Fn &&f) {
+  if (P > 2 * kTailNT)
+    tail_entries_u<8>(pos, nn, P, s_ws, tb, f);
+  else
+    tail_entries_u<2>(pos, nn, P, s_ws, tb, f);
+}
+
 template <int DT>
 __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
   __shared__ int32_t s_size[kTailNodes], s_minpt[kTailNodes];
@@ -2504,7 +2557,7 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
   // a round's new windows when they fit: built here, then copied out
   __shared__ uint64_t s_win[kTailWin];
   __shared__ int32_t wsum[kTailNT / kWave];
-  __shared__ int32_t s_any, s_flag, s_cnt, s_ne;
+  __shared__ int32_t s_any, s_flag, s_ne, s_nm, s_nr, s_need;
   __shared__ long long s_cut;
   __shared__ double s_lambda[kTailLevels];
   __shared__ long long s_smin[kTailLevels];
@@ -2532,7 +2585,7 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
     s_size[v] = t.size[v];
     s_minpt[v] = t.minpt[v];
     s_ws[v] = t.ws[tc][v];
-    s_wl[v] = t.wl[tc][v];
+    s_wl[v] = s_deg[v] = t.wl[tc][v];
     s_Mt[v] = v;
     s_live[v] = 1;
     s_mrg[v] = 0;
@@ -2540,28 +2593,26 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
     s_touch[v] = 0;
     s_sel[v] = v;
   }
-  if (threadIdx.x == 0) s_cnt = 0;
   __syncthreads();
   // every live row's entries (the incoming windows are packed end to end)
-  int32_t top = 0;
-  {
-    const int32_t P =
-        tail_scan(N, [&](int32_t v) { return s_wl[v]; }, s_pos, wsum);
-    top = s_ws[N - 1] + s_wl[N - 1];
-    for (int32_t v = threadIdx.x; v < N; v += kTailNT) s_deg[v] = 0;
-    __syncthreads();
-    tail_entries(s_pos, N, P, s_ws, t.tbl[tc],
-                 [&](int32_t, int32_t v, uint64_t) { atomicAdd(&s_deg[v], 1); });
-    __syncthreads();
-  }
+  int32_t top = s_ws[N - 1] + s_wl[N - 1];
+  const int32_t packed = top;
   int32_t nn = N;  // live nodes
-  int32_t ed = tail_scan(N, [&](int32_t v) { return s_deg[v]; }, s_nws, wsum);
+  int32_t new0 = 0, new1 = 0;  // slots of the last round's new windows
+  int32_t ed = 0;
+  for (int32_t v = threadIdx.x; v < N; v += kTailNT) ed += s_wl[v];
+  ed = tail_sum(ed, wsum);
+  if (packed > t.gcap) {
+    if (threadIdx.x == 0) raise_err(ctl, kErrInternal);
+    return;
+  }
   for (int32_t l = t.level0; l < t.n_levels; ++l) {
     const double lambda = s_lambda[l];
     const long long smin = s_smin[l];
     for (int32_t round = (l == t.level0 ? t.round0 : 0);; ++round) {
       if (ed == 0 || nn == 1) break;  // nothing can merge
-      const bool fresh = round == 0 || (l == t.level0 && round == t.round0);
+      const bool start = l == t.level0 && round == t.round0;
+      const bool fresh = round == 0 || start;
       if (round >= t.max_rounds) {
         if (threadIdx.x == 0) {
           ctl->tail_level = l;
@@ -2570,7 +2621,7 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
         return;
       }
       const uint64_t *tb = t.tbl[tc];
-      if (threadIdx.x == 0) s_any = 0;
+      if (threadIdx.x == 0) s_any = s_ne = s_nm = s_nr = s_need = 0;
       for (int32_t v = threadIdx.x; v < N; v += kTailNT) {
         s_key[v] = 0ull;
         s_pick[v] = ~0ull;
@@ -2580,53 +2631,85 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
       auto scanned = [&](int32_t v) {
         return s_live[v] && (fresh || s_mrg[v]);
       };
-      if (threadIdx.x == 0) s_ne = 0;
-      const int32_t P = tail_scan(
-          N, [&](int32_t v) { return scanned(v) ? s_wl[v] : 0; }, s_pos, wsum);
       // the edges to evaluate, each once: from the row of its smaller end
       // when both rows are scanned
-      tail_entries<8>(s_pos, N, P, s_ws, tb, [&](int32_t, int32_t v,
-                                                 uint64_t e) {
-        const int32_t u = (int32_t)(e >> 32);
-        if ((uint32_t)u >= (uint32_t)N || !s_live[u]) {
+      auto list_edge = [&](uint64_t e) {
+        const int32_t v = tail_v(e), u = tail_u(e);
+        if (u >= N || !s_live[u]) {
           raise_err(ctl, kErrInternal);
           return;
         }
         if (u < v && scanned(u)) return;
         const int32_t i = atomicAdd(&s_ne, 1);
-        const uint64_t le =
-            ((uint64_t)(uint32_t)(v | (u << 16)) << 32) | (uint32_t)e;
         if (i < kLE)
-          s_el[i] = le;
+          s_el[i] = e;
         else if (i < t.gcap)
-          t.elist[i] = le;
+          t.elist[i] = e;
         else
           raise_err(ctl, kErrInternal);
-      });
-      __syncthreads();
-      const int32_t ne = min(s_ne, t.gcap);
+      };
+      if (start) {
+        // the packed slots themselves, their gains made by k_repack
+        __syncthreads();
+      } else if (fresh) {
+        const int32_t P = tail_scan(
+            N, [&](int32_t v) { return s_live[v] ? s_wl[v] : 0; }, s_pos,
+            wsum);
+        tail_entries(s_pos, N, P, s_ws, tb,
+                     [&](int32_t, int32_t, uint64_t e) { list_edge(e); });
+        __syncthreads();
+      } else {
+        // the rows of the nodes formed by a merge lie in the last round's
+        // new windows, among others
+        __syncthreads();
+        for (int32_t p0 = new0 + (int32_t)threadIdx.x; p0 < new1;
+             p0 += 4 * kTailNT) {
+          uint64_t ev[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int32_t p = p0 + j * kTailNT;
+            ev[j] = p < new1 ? tb[p] : kEmpty;
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (ev[j] != kEmpty && s_mrg[tail_v(ev[j])]) list_edge(ev[j]);
+        }
+        __syncthreads();
+      }
+      const int32_t ne = start ? packed : min(s_ne, t.gcap);
+      // edge i: from the packed slots (both ends' entries are there, the
+      // larger end's is skipped) or from the list
+      auto edge_at = [&](int32_t i) -> uint64_t {
+        return start ? tb[i] : (i < kLE ? s_el[i] : t.elist[i]);
+      };
       // Steps 1-2, pass 1: each listed edge's gain, and each end's largest
       // candidate gain (two edges per thread in flight)
       for (int32_t i0 = threadIdx.x; i0 < ne; i0 += 2 * kTailNT) {
         uint64_t ev[2];
+        double gv[2] = {0.0, 0.0};
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           const int32_t i = min(i0 + j * kTailNT, ne - 1);
-          ev[j] = i < kLE ? s_el[i] : t.elist[i];
+          ev[j] = edge_at(i);
+          if (start) gv[j] = t.gain[i];
         }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           const int32_t i = i0 + j * kTailNT;
           if (i >= ne) break;
-          const uint32_t vu = (uint32_t)(ev[j] >> 32);
-          const int32_t v = (int32_t)(vu & 0xffffu), u = (int32_t)(vu >> 16);
+          const int32_t v = tail_v(ev[j]), u = tail_u(ev[j]);
           const int32_t w = (int32_t)(uint32_t)ev[j];
-          const double g = tail_gain<DT>(t.mu, v, u, d, (double)s_size[v],
-                                         (double)s_size[u], w, lambda);
-          if (i < kLE)
-            s_gn[i] = g;
-          else
-            t.gain[i] = g;
+          double g = gv[j];
+          if (!start) {
+            g = tail_gain<DT>(t.mu, v, u, d, (double)s_size[v],
+                              (double)s_size[u], w, lambda);
+            if (i < kLE)
+              s_gn[i] = g;
+            else
+              t.gain[i] = g;
+          } else if (ev[j] == kEmpty || u < v) {
+            continue;
+          }
           const unsigned long long kg = gain_key(g);
           if (g > 0.0 || (long long)s_size[v] < smin) atomicMax(&s_key[v], kg);
           if (g > 0.0 || (long long)s_size[u] < smin) atomicMax(&s_key[u], kg);
@@ -2642,14 +2725,14 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
 #pragma unroll
         for (int j = 0; j < kTU; ++j) {
           const int32_t i = min(i0 + j * kTailNT, ne - 1);  // no branch
-          ev[j] = i < kLE ? s_el[i] : t.elist[i];
-          gv[j] = i < kLE ? s_gn[i] : t.gain[i];
+          ev[j] = edge_at(i);
+          gv[j] = !start && i < kLE ? s_gn[i] : t.gain[i];
         }
 #pragma unroll
         for (int j = 0; j < kTU; ++j) {
           if (i0 + j * kTailNT >= ne) break;
-          const uint32_t vu = (uint32_t)(ev[j] >> 32);
-          const int32_t v = (int32_t)(vu & 0xffffu), u = (int32_t)(vu >> 16);
+          const int32_t v = tail_v(ev[j]), u = tail_u(ev[j]);
+          if (start && (ev[j] == kEmpty || u < v)) continue;
           const unsigned long long kv = s_key[v], ku = s_key[u];
           const unsigned long long kg = gain_key(gv[j]);
           if (kv != 0ull && kg == kv)
@@ -2698,32 +2781,27 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
       }
       // Step 4 statistics: members add into their roots (size and smallest
       // point in LDS, the sums in global memory)
-      int32_t members = 0;
       for (int32_t v = threadIdx.x; v < N; v += kTailNT) {
         const int32_t r = s_sel[v];
         if (s_live[v] && r != v) {
-          ++members;
           s_new[r] = 1;
           atomicAdd(&s_size[r], s_size[v]);
           atomicMin(&s_minpt[r], s_minpt[v]);
         }
       }
-      members = wave_sum(members);
-      if (lane == 0 && members) atomicAdd(&s_cnt, members);
+      __syncthreads();
       // lists of the members (in s_L, free after the hook) and of the
       // merged roots (in s_pick, free after the choices)
       int32_t *s_ml = s_L;
       int32_t *s_rl = reinterpret_cast<int32_t *>(s_pick);
-      const int32_t nm = tail_scan(
-          N, [&](int32_t v) { return (s_live[v] && s_sel[v] != v) ? 1 : 0; },
-          s_pos, wsum);
-      for (int32_t v = threadIdx.x; v < N; v += kTailNT)
-        if (s_live[v] && s_sel[v] != v) s_ml[s_pos[v]] = v;
-      const int32_t nr =
-          tail_scan(N, [&](int32_t v) { return (int32_t)s_new[v]; }, s_nws, wsum);
-      for (int32_t v = threadIdx.x; v < N; v += kTailNT)
-        if (s_new[v]) s_rl[s_nws[v]] = v;
+      for (int32_t v0 = 0; v0 < N; v0 += kTailNT) {
+        const int32_t v = v0 + (int32_t)threadIdx.x;
+        const bool in = v < N;
+        tail_append(in && s_live[v] && s_sel[v] != v, v, s_ml, &s_nm);
+        tail_append(in && s_new[v], v, s_rl, &s_nr);
+      }
       __syncthreads();
+      const int32_t nm = s_nm, nr = s_nr;
       // the members' sums, one (member, dimension) pair per thread
       for (int32_t q0 = threadIdx.x; q0 < nm * d; q0 += kTU * kTailNT) {
         int64_t sv[kTU];
@@ -2750,13 +2828,10 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
             return (s_live[v] && s_sel[v] != v) ? s_wl[v] : 0;
           },
           s_pos, wsum);
-      tail_entries<8>(s_pos, N, Pm, s_ws, tb,
-                      [&](int32_t, int32_t, uint64_t e) {
-                        const int32_t u = (int32_t)(e >> 32);
-                        if ((uint32_t)u < (uint32_t)N && s_sel[u] == u &&
-                            !s_new[u])
-                          s_touch[u] = 1;
-                      });
+      tail_entries(s_pos, N, Pm, s_ws, tb, [&](int32_t, int32_t, uint64_t e) {
+        const int32_t u = tail_u(e);
+        if (u < N && s_sel[u] == u && !s_new[u]) s_touch[u] = 1;
+      });
       __syncthreads();
       // Step 4 means of the merged roots (their sums are complete)
       for (int32_t q0 = threadIdx.x; q0 < nr * d; q0 += kTU * kTailNT) {
@@ -2784,8 +2859,23 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
       for (int32_t v = threadIdx.x; v < N; v += kTailNT)
         if (s_live[v] && rebuilt(s_sel[v])) atomicAdd(&s_cap[s_sel[v]], s_deg[v]);
       __syncthreads();
-      int32_t need = tail_scan(
-          N, [&](int32_t A) { return rebuilt(A) ? s_cap[A] : 0; }, s_nws, wsum);
+      // the windows' places, in no particular order: a scan a wave, one
+      // atomic on the total
+      auto place = [&]() {
+        for (int32_t v0 = 0; v0 < N; v0 += kTailNT) {
+          const int32_t A = v0 + (int32_t)threadIdx.x;
+          const int32_t c = A < N && rebuilt(A) ? s_cap[A] : 0;
+          const int32_t inc = wave_incl_scan(c);
+          const int32_t all = wave_last(inc);
+          int32_t at = 0;
+          if (lane == 0 && all) at = atomicAdd(&s_need, all);
+          at = __builtin_amdgcn_readfirstlane(at);
+          if (A < N) s_nws[A] = at + inc - c;
+        }
+        __syncthreads();
+        return s_need;
+      };
+      int32_t need = place();
       // room for the new windows past the end of the table, else every
       // live row is rebuilt into the other buffer
       int spread = 2;
@@ -2795,6 +2885,8 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
           spread = 1;
         } else {
           whole = true;
+          __syncthreads();  // all have read s_need
+          if (threadIdx.x == 0) s_need = 0;
           for (int32_t v = threadIdx.x; v < N; v += kTailNT) {
             s_cap[v] = 0;
             if (s_live[v] && s_sel[v] == v) s_touch[v] = 1;
@@ -2803,9 +2895,7 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
           for (int32_t v = threadIdx.x; v < N; v += kTailNT)
             if (s_live[v]) atomicAdd(&s_cap[s_sel[v]], s_deg[v]);
           __syncthreads();
-          need = tail_scan(
-              N, [&](int32_t A) { return rebuilt(A) ? s_cap[A] : 0; }, s_nws,
-              wsum);
+          need = place();
           spread = 2 * need <= t.tcap ? 2 : 1;
           if (need > t.tcap) {
             if (threadIdx.x == 0) raise_err(ctl, kErrInternal);
@@ -2851,10 +2941,9 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
         for (int j = 0; j < kIU; ++j) {
           const int32_t v = vv[j];
           const uint64_t e = tb[s_ws[v] + (pp[j] - s_pos[v])];
-          const int32_t u = (int32_t)(e >> 32);
+          const int32_t u = tail_u(e);
           A[j] = s_sel[v];
-          B[j] = (e != kEmpty && (uint32_t)u < (uint32_t)N &&
-                  p0 + j * kTailNT < Ps)
+          B[j] = (e != kEmpty && u < N && p0 + j * kTailNT < Ps)
                      ? s_sel[u]
                      : A[j];  // nothing to add
           W[j] = (int32_t)(uint32_t)e;
@@ -2872,9 +2961,8 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
             if (pend[j])
               got[j] = __hip_atomic_compare_exchange_strong(
                   win + spread * s_nws[A[j]] + h[j], &cur[j],
-                  ((uint64_t)(uint32_t)B[j] << 32) | (uint32_t)W[j],
-                  __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                  __HIP_MEMORY_SCOPE_WORKGROUP);
+                  tail_entry(A[j], B[j], (uint32_t)W[j]), __ATOMIC_RELAXED,
+                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           }
           any = false;
 #pragma unroll
@@ -2884,7 +2972,7 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
             if (got[j]) {
               atomicAdd(&s_ndeg[A[j]], 1);
               pend[j] = false;
-            } else if ((int32_t)(cur[j] >> 32) == B[j]) {
+            } else if (tail_u(cur[j]) == B[j]) {
               __hip_atomic_fetch_add(win + spread * s_nws[A[j]] + h[j],
                                      (uint64_t)(uint32_t)W[j], __ATOMIC_RELAXED,
                                      __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -2930,12 +3018,13 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
         s_touch[v] = 0;
         s_sel[v] = v;
       }
-      nn -= s_cnt;
-      top = base + spread * need;
+      nn -= nm;
+      new0 = base;
+      new1 = top = base + spread * need;
       tc = tn;
-      ed = tail_scan(N, [&](int32_t v) { return s_deg[v]; }, s_nws, wsum);
-      if (threadIdx.x == 0) s_cnt = 0;
-      __syncthreads();
+      int32_t mine = 0;
+      for (int32_t v = threadIdx.x; v < N; v += kTailNT) mine += s_deg[v];
+      ed = tail_sum(mine, wsum);
     }
     // level end: live nodes numbered in id order, snapshots for the labels
     // and the energy
@@ -3027,28 +3116,51 @@ __global__ __launch_bounds__(256) void k_tail_labels(
 
 // Rows of the table the tail starts from, copied into windows packed end
 // to end, each row's entries moved to the front of its window (wl2 = the
-// entry count).  A wave per row, lanes striding over its slots (hub rows
-// are long).
+// entry count) in the tail's form.  A wave per row, lanes striding over its
+// slots (hub rows are long).  The gains of the tail's first round are made
+// here, slot by slot from each edge's smaller end: a thousand waves on the
+// whole chip, where the tail's one CU took 52 us for 5,000 edges at D = 32.
+template <int DT>
 __global__ __launch_bounds__(256) void k_repack(
     int32_t nn, const int32_t *__restrict__ ws, const int32_t *__restrict__ wl,
     const uint64_t *__restrict__ tbl, const int32_t *__restrict__ ws2,
-    int32_t *__restrict__ wl2, uint64_t *__restrict__ tbl2) {
+    int32_t *__restrict__ wl2, uint64_t *__restrict__ tbl2,
+    const int32_t *__restrict__ size, const double *__restrict__ mu,
+    int32_t dr, double lambda, double *__restrict__ gain, int32_t gcap,
+    Ctl *ctl) {
   const int lane = threadIdx.x & (kWave - 1);
+  const int32_t d = DT > 0 ? DT : dr;
   const int32_t v = (int32_t)(blockIdx.x * (blockDim.x / kWave) +
                               threadIdx.x / kWave);
   if (v >= nn) return;
   const int32_t len = wl[v];
   const uint64_t *src = tbl + ws[v];
-  uint64_t *dst = tbl2 + ws2[v];
+  const int32_t base = ws2[v];
+  const double dsv = (double)size[v];
   int32_t cnt = 0;
   for (int32_t j0 = 0; j0 < len; j0 += kWave) {
     const int32_t j = j0 + lane;
     const uint64_t e = j < len ? src[j] : kEmpty;
     const uint64_t m = __ballot(e != kEmpty);
-    if (e != kEmpty)
-      dst[cnt + __popcll(m & ((1ull << lane) - 1ull))] = e;
+    if (e != kEmpty) {
+      const int32_t u = (int32_t)(e >> 32);
+      const int32_t w = (int32_t)(uint32_t)e;
+      const int32_t at =
+          base + cnt + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+      if ((uint32_t)u >= (uint32_t)nn || at >= gcap) {
+        raise_err(ctl, kErrInternal);
+      } else {
+        tbl2[at] = tail_entry(v, u, (uint32_t)w);
+        if (v < u)
+          gain[at] = tail_gain<DT>(mu, v, u, d, dsv, (double)size[u], w,
+                                   lambda);
+      }
+    }
     cnt += __popcll(m);
   }
+  // the rest of the window is empty (passes over slots run through it)
+  for (int32_t j = cnt + lane; j < len; j += kWave)
+    if (base + j < gcap) tbl2[base + j] = kEmpty;
   if (lane == 0) wl2[v] = cnt;
 }
 
@@ -4682,8 +4794,18 @@ int run_tail(const LadderArgs &g, const Bufs &b, const float *emb,
   const int nxt = 1 - cur;
   device_scan(ScanArray{b.wl[cur], b.ws[nxt], nn, nullptr}, nn + 1, b.bsum,
               b.tmp, st);
-  hipLaunchKernelGGL(k_repack, blocks_for((int64_t)nn * kWave), dim3(256), 0, st, nn, b.ws[cur],
-                     b.wl[cur], b.tbl[cur], b.ws[nxt], b.wl[nxt], b.tbl[nxt]);
+#define EZSP_REPACK(DT)                                                       \
+  hipLaunchKernelGGL(k_repack<DT>, blocks_for((int64_t)nn * kWave), dim3(256), \
+                     0, st, nn, b.ws[cur], b.wl[cur], b.tbl[cur], b.ws[nxt],  \
+                     b.wl[nxt], b.tbl[nxt], b.size[cur], b.mu, d,             \
+                     g.lambdas[level0], b.tgain, b.tslots, ctl)
+  switch (d) {
+    case 8: EZSP_REPACK(8); break;
+    case 16: EZSP_REPACK(16); break;
+    case 32: EZSP_REPACK(32); break;
+    default: EZSP_REPACK(0);
+  }
+#undef EZSP_REPACK
   t.tcur0 = nxt;
   t.d = d;
   t.tcap = (int32_t)(2 * edge_bound(n, g.k));
