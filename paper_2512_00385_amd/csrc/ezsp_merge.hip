@@ -697,30 +697,40 @@ __global__ __launch_bounds__(256) void k_select(
   }
   Best b{0.0, -1, -1};  // mp < 0: not loaded yet
   int32_t cnt = 0;
-  bool skip = false;
+  // A node that did not merge had no candidate last round, and its edges to
+  // others that did not merge have the same gains now: only its edges to
+  // merged nodes can be candidates.  Its row is scanned for those first
+  // (bit i of `hits`: entry lg + i G), four entries of a lane in flight, and
+  // only they fetch mean rows.  (Evaluating every edge of a row with one
+  // merged neighbour took 1.7 ms a round at 9.8M nodes, 2 % of them merged.)
+  bool part = false;
+  uint32_t hits = 0;
+  static_assert(FIRST || kLongRow / G <= 32, "a bit per entry of a lane");
   if constexpr (!FIRST) {
-    // A node that did not merge, with no neighbour that merged, has the
-    // gains of the last round, which gave it no candidate: no candidate now.
-    if (s.merged) {
-      int32_t any = 0, c0 = 0;
-      if (live) {
-        any = s.merged[v];
-        if (!any)  // a merged node is evaluated anyway: no scan for it
-          for_row<false>(a, v, lg, G, [&](int32_t u, int32_t) {
-            ++c0;
-            if ((uint32_t)u < (uint32_t)nn) any |= s.merged[u];
-          });
-      }
+    if (s.merged && live && !s.merged[v]) {
+      part = true;
+      const uint64_t *t = a.tbl + a.ws[v];
+      for (int32_t i0 = 0; lg + i0 * G < span; i0 += 4) {
+        uint64_t ev[4];
 #pragma unroll
-      for (int off = G / 2; off > 0; off >>= 1)
-        any |= __shfl_xor(any, off, kWave);
-      if (!any) {
-        skip = true;
-        cnt = c0;
+        for (int q = 0; q < 4; ++q) {
+          const int32_t j = lg + (i0 + q) * G;
+          ev[q] = j < span ? t[j] : kEmpty;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int32_t u = (int32_t)(ev[q] >> 32);
+          if (ev[q] == kEmpty) continue;
+          ++cnt;
+          if ((uint32_t)u >= (uint32_t)nn)
+            raise_err(ctl, kErrInternal);
+          else if (s.merged[u])
+            hits |= 1u << (i0 + q);
+        }
       }
     }
   }
-  if (live && !skip) {
+  if (live && (!part || hits)) {
     const int F = ctl->F;
     const double sF = ldexp(1.0, F), sIF = ldexp(1.0, -F);
     const int32_t sv = node_size<FIRST>(s, v);
@@ -728,12 +738,7 @@ __global__ __launch_bounds__(256) void k_select(
     const bool small = (int64_t)sv < smin;
     MeanRow<FIRST, DT> mv;
     mv.load(s, v, sF, sIF);
-    for_row<FIRST>(a, v, lg, G, [&](int32_t u, int32_t w) {
-      ++cnt;
-      if ((uint32_t)u >= (uint32_t)nn) {
-        raise_err(ctl, kErrInternal);
-        return;
-      }
+    auto evaluate = [&](int32_t u, int32_t w) {
       const double g =
           edge_gain_t<FIRST, DT>(s, mv, v, dsv, u, w, d, lambda, sF, sIF);
       // the smallest point only breaks a tie of equal gains: loaded for a
@@ -747,7 +752,22 @@ __global__ __launch_bounds__(256) void k_select(
           if (mp < b.mp) b = Best{g, mp, u};
         }
       }
-    });
+    };
+    if (part) {
+      const uint64_t *t = a.tbl + a.ws[v];
+      for (uint32_t h = hits; h; h &= h - 1) {
+        const uint64_t e = t[lg + __builtin_ctz(h) * G];
+        evaluate((int32_t)(e >> 32), (int32_t)(uint32_t)e);
+      }
+    } else {
+      for_row<FIRST>(a, v, lg, G, [&](int32_t u, int32_t w) {
+        ++cnt;
+        if ((uint32_t)u >= (uint32_t)nn)
+          raise_err(ctl, kErrInternal);
+        else
+          evaluate(u, w);
+      });
+    }
     if (b.u >= 0 && b.mp < 0) b.mp = node_minpt<FIRST>(s, b.u);
   }
   if constexpr (G > 1) {
@@ -941,6 +961,8 @@ __global__ __launch_bounds__(256) void k_select_long(
     mv.load(s, v, sF, sIF);
     Best b{0.0, 0, -1};
     int32_t cnt = 0;
+    // a row that did not merge: only its edges to merged nodes (k_select)
+    const bool part = !FIRST && s.merged && !s.merged[v];
     for (int32_t j = j0 + lane; j < j1; j += kWave) {
       int32_t u, w;
       if (!row_entry_at<FIRST>(a, v, rb, j, u, w)) continue;
@@ -949,6 +971,7 @@ __global__ __launch_bounds__(256) void k_select_long(
         raise_err(ctl, kErrInternal);
         continue;
       }
+      if (part && !s.merged[u]) continue;
       const double g =
           edge_gain_t<FIRST, DT>(s, mv, v, dsv, u, w, d, lambda, sF, sIF);
       if (g > 0.0 || small) {
@@ -1140,7 +1163,7 @@ struct ScanWindows {
   int32_t *toff;
   const int32_t *n_dev;
   int32_t *cstart;
-  int32_t chunk, qcap;
+  int32_t shift, qcap;  // chunks of 1 << shift slots
   Ctl *ctl;
   __device__ int32_t value(int32_t i) const {
     return (i < *n_dev) ? cap[i] : 0;
@@ -1156,10 +1179,10 @@ struct ScanWindows {
     toff[i] = excl;
     if (i == 0) put(0, 0);
     if (i < len) {
-      for (int32_t q = excl / chunk + 1; q <= (excl + v) / chunk; ++q)
+      for (int32_t q = (excl >> shift) + 1; q <= (excl + v) >> shift; ++q)
         put(q, i + 1);
-    } else if (excl % chunk != 0) {
-      put(excl / chunk + 1, len);
+    } else if (excl & ((1 << shift) - 1)) {
+      put((excl >> shift) + 1, len);
     }
   }
 };
@@ -4470,8 +4493,8 @@ void launch_round(const Bufs &b, const Adj &adj, int cur, int32_t n,
   }
   prof_end(st);
   prof_begin("contract", st);
-  device_scan(ScanWindows{b.capn, b.ws[nxt], &ctl->n_next, b.cstart, chunk,
-                          b.qcap, ctl},
+  device_scan(ScanWindows{b.capn, b.ws[nxt], &ctl->n_next, b.cstart,
+                          __builtin_ctz((unsigned)chunk), b.qcap, ctl},
               nn + 1, b.bsum, &ctl->slots, st);
   hipLaunchKernelGGL(k_contract_chunk<FIRST>,
                      dim3(xcd_grid((ed + chunk - 1) / chunk)), dim3(256), 0,
