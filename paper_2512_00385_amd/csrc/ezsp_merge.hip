@@ -1148,7 +1148,7 @@ struct ScanRoots {
   }
   __device__ void emit(int32_t v, int32_t excl, int32_t val) const {
     if (val) newid[v] = excl;
-    if (v < nn) cnt[v] = 0;
+    if (v < nn) cnt[v] = 1;  // the root; k_assign counts the others
   }
 };
 
@@ -1179,8 +1179,10 @@ struct ScanWindows {
     toff[i] = excl;
     if (i == 0) put(0, 0);
     if (i < len) {
-      for (int32_t q = (excl >> shift) + 1; q <= (excl + v) >> shift; ++q)
-        put(q, i + 1);
+      // (a window of more than a chunk: k_clear_big, with a block or all)
+      if (v <= (1 << shift))
+        for (int32_t q = (excl >> shift) + 1; q <= (excl + v) >> shift; ++q)
+          put(q, i + 1);
     } else if (excl & ((1 << shift) - 1)) {
       put((excl >> shift) + 1, len);
     }
@@ -1188,9 +1190,11 @@ struct ScanWindows {
 };
 
 // Component of every node and its place among the component's members.
-// Nodes of one component mostly sit together in node order, so the lanes
-// of a wave are grouped by component (ballot per distinct value) and each
-// group takes its places with one atomic, made by its lowest lane.
+// The root is the first member, without an atomic: most nodes are roots
+// (10M nodes of a round in which 2 % merge: 193 -> 75 us).  Other nodes of
+// one component mostly sit together in node order, so the lanes of a wave are
+// grouped by component (ballot per distinct value) and each group takes its
+// places with one atomic, made by its lowest lane.
 __global__ __launch_bounds__(256) void k_assign(int32_t nn,
                                                 const int32_t *parent,
                                                 const int32_t *newid,
@@ -1199,9 +1203,11 @@ __global__ __launch_bounds__(256) void k_assign(int32_t nn,
   if (!round_live(ctl)) return;
   const int32_t v = xcd_tid();
   const bool act = v < nn;
+  bool member = false;
   int32_t c = -1;
   if (act) {
     const int32_t r = parent[v];
+    member = r != v;
     c = 0;
     if ((uint32_t)r < (uint32_t)nn) {
       c = newid[r];
@@ -1215,13 +1221,13 @@ __global__ __launch_bounds__(256) void k_assign(int32_t nn,
     L[v] = c;
   }
   const int lane = threadIdx.x & (kWave - 1);
-  uint64_t todo = __ballot(act);
+  uint64_t todo = __ballot(member);
   uint64_t mine = 0;
   int leader = 0;
   while (todo) {
     const int l = __builtin_ctzll(todo);
     const int32_t cl = __shfl(c, l, kWave);
-    const uint64_t m = __ballot(c == cl) & todo;
+    const uint64_t m = __ballot(member && c == cl) & todo;
     if ((m >> lane) & 1) {
       mine = m;
       leader = l;
@@ -1229,9 +1235,10 @@ __global__ __launch_bounds__(256) void k_assign(int32_t nn,
     todo &= ~m;
   }
   int32_t base = 0;
-  if (act && lane == leader) base = atomicAdd(&cnt[c], __popcll(mine));
+  if (member && lane == leader) base = atomicAdd(&cnt[c], __popcll(mine));
   base = __shfl(base, leader, kWave);
-  if (act) rank[v] = base + __popcll(mine & ((1ull << lane) - 1));
+  if (act)
+    rank[v] = member ? base + __popcll(mine & ((1ull << lane) - 1)) : 0;
 }
 
 // Members in component order; the first member of each component also
@@ -1981,20 +1988,45 @@ __global__ __launch_bounds__(256) void k_contract_chunk(
 // tiles of 256 members are pre-aggregated in an LDS table (one component per
 // tile, keyed by neighbour) and flushed into the window with atomics.  Rows
 // keep their empty slots.
+//
+// The clearing also writes the chunk starts inside these windows, ahead of
+// k_contract_chunk.  A block takes a window, and all blocks share each giant
+// one: a block alone, and a thread alone with its chunk starts, took 0.4 and
+// 0.16 ms for a window of millions of slots.
+constexpr int32_t kGiantWin = 1 << 16;
+
 __global__ __launch_bounds__(256) void k_clear_big(
     const int32_t *__restrict__ cbig, const int32_t *__restrict__ toff,
-    const int32_t *__restrict__ cap, uint64_t *tbl, int32_t tcap, Ctl *ctl) {
+    const int32_t *__restrict__ cap, uint64_t *tbl, int32_t tcap,
+    int32_t *__restrict__ cstart, int32_t shift, int32_t qcap, Ctl *ctl) {
+  __shared__ int32_t giant[256];
+  __shared__ int32_t n_giant;
   if (!round_live(ctl)) return;
   const int32_t nb = ctl->n_cbig;
-  for (int32_t bi = blockIdx.x; bi < nb; bi += gridDim.x) {
-    const int32_t c = cbig[bi];
+  auto clear = [&](int32_t c, int32_t first, int32_t step) {
     const int32_t base = toff[c], cp = cap[c];
-    if (base < 0 || base + cp > tcap) {
+    if (base < 0 || base + cp > tcap || (base + cp) >> shift >= qcap) {
       raise_err(ctl, kErrInternal);
-      continue;
+      return;
     }
-    for (int32_t t = threadIdx.x; t < cp; t += blockDim.x)
-      tbl[base + t] = kEmpty;
+    for (int32_t t = first; t < cp; t += step) tbl[base + t] = kEmpty;
+    for (int32_t q = (base >> shift) + 1 + first; q <= (base + cp) >> shift;
+         q += step)
+      cstart[q] = c + 1;
+  };
+  for (int32_t bi = blockIdx.x; bi < nb; bi += gridDim.x)
+    if (cap[cbig[bi]] <= kGiantWin) clear(cbig[bi], threadIdx.x, blockDim.x);
+  for (int32_t b0 = 0; b0 < nb; b0 += 256) {
+    __syncthreads();
+    if (threadIdx.x == 0) n_giant = 0;
+    __syncthreads();
+    const int32_t bi = b0 + (int32_t)threadIdx.x;
+    if (bi < nb && cap[cbig[bi]] > kGiantWin)
+      giant[atomicAdd(&n_giant, 1)] = cbig[bi];
+    __syncthreads();
+    for (int32_t g = 0; g < n_giant; ++g)
+      clear(giant[g], blockIdx.x * blockDim.x + threadIdx.x,
+            gridDim.x * blockDim.x);
   }
 }
 
@@ -4493,15 +4525,17 @@ void launch_round(const Bufs &b, const Adj &adj, int cur, int32_t n,
   }
   prof_end(st);
   prof_begin("contract", st);
-  device_scan(ScanWindows{b.capn, b.ws[nxt], &ctl->n_next, b.cstart,
-                          __builtin_ctz((unsigned)chunk), b.qcap, ctl},
+  const int32_t shift = __builtin_ctz((unsigned)chunk);
+  device_scan(ScanWindows{b.capn, b.ws[nxt], &ctl->n_next, b.cstart, shift,
+                          b.qcap, ctl},
               nn + 1, b.bsum, &ctl->slots, st);
+  hipLaunchKernelGGL(k_clear_big, big_grid, dim3(256), 0, st, b.cbig,
+                     b.ws[nxt], b.capn, b.tbl[nxt], tcap, b.cstart, shift,
+                     b.qcap, ctl);
   hipLaunchKernelGGL(k_contract_chunk<FIRST>,
                      dim3(xcd_grid((ed + chunk - 1) / chunk)), dim3(256), 0,
                      st, nn, adj, b.L, b.mem, b.moff, b.ws[nxt], b.capn,
                      b.cstart, b.tbl[nxt], b.wl[nxt], chunk, ctl);
-  hipLaunchKernelGGL(k_clear_big, big_grid, dim3(256), 0, st, b.cbig,
-                     b.ws[nxt], b.capn, b.tbl[nxt], tcap, ctl);
   hipLaunchKernelGGL(k_contract_big<FIRST>, big_grid, dim3(256), 0, st, nn,
                      adj, b.L, b.mem, b.moff, b.ws[nxt], b.capn, b.tile_c,
                      b.tile_i, b.tbl[nxt], tcap, ctl);
