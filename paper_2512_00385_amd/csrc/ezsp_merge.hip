@@ -68,6 +68,17 @@ __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
     p[i] = v;
 }
 
+// The arrays that a ladder starts from zero: the reverse lists' counts and
+// cursors, and the giant components' partial sums.
+__global__ void k_start_zero(int32_t *rev, int32_t *cursor, int64_t n,
+                             unsigned long long *gsum, int64_t ng) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+       i < n || i < ng; i += (int64_t)gridDim.x * blockDim.x) {
+    if (i < n) rev[i] = cursor[i] = 0;
+    if (i < ng) gsum[i] = 0;
+  }
+}
+
 // Rows of 4k floats: 16-byte moves, and the max |e| of Step 0's fixed-point
 // shift (with the non-finite check) taken on the way, striped per block.
 __global__ __launch_bounds__(256) void k_gather_rows4(const float4 *emb,
@@ -1519,23 +1530,37 @@ __global__ __launch_bounds__(256) void k_stats_s(
 // k_stats_big for D = DT: one pass over the members, each thread summing
 // whole rows (16-byte loads, two members in flight), then a block
 // reduction (exact int64, so the order does not matter).
+// Partial sums of a giant component, joined by the blocks that share it:
+// the dimensions, then size, summed degree, INT32_MAX - smallest point, and
+// the segments done.  All zero between uses.
+constexpr int32_t kGiantMembers = 4096;
+constexpr int32_t kGiantSeg = 1024;     // members a block takes at a time
+constexpr int32_t kGiantSlots = 4096;   // of the list of big components
+constexpr int32_t kGiantStride = 64 + 4;
+
+// A block per component of more than big_members members; the blocks share
+// each of more than kGiantMembers, segment by segment, and the block that
+// ends the last segment writes the component.  (A giant component alone on
+// one block took 0.83 ms at 200,000 members.)
 template <bool FIRST, int DT>
 __global__ __launch_bounds__(256) void k_stats_big_t(
     const int32_t *__restrict__ mem, const int32_t *__restrict__ moff,
     NodeIn s, const int32_t *__restrict__ deg, NodeOut o,
-    const int32_t *__restrict__ big, Ctl *ctl) {
-  static_assert(DT > 0 && DT % 4 == 0, "vector rows");
+    const int32_t *__restrict__ big, unsigned long long *gsum, int32_t gslots,
+    Ctl *ctl) {
+  static_assert(DT > 0 && DT % 4 == 0 && DT <= 64, "vector rows");
   constexpr int kU = 2;
   constexpr int NW = 256 / kWave;
   __shared__ long long sS[NW][DT];
   __shared__ int32_t ssize[NW], smp[NW], scap[NW];
+  __shared__ int32_t giant[256];
+  __shared__ int32_t n_giant, last;
   if (!round_live(ctl)) return;
   const double sF = ldexp(1.0, ctl->F), sIF = ldexp(1.0, -ctl->F);
   const int32_t n_big = ctl->n_big;
   const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  for (int32_t bi = blockIdx.x; bi < n_big; bi += gridDim.x) {
-    const int32_t c = big[bi];
-    const int32_t m0 = moff[c], m1 = moff[c + 1];
+  // the waves' sums over the members [m0, m1) of the list, to LDS
+  auto sum_members = [&](int32_t m0, int32_t m1) {
     int64_t acc[DT];
 #pragma unroll
     for (int q = 0; q < DT; ++q) acc[q] = 0;
@@ -1591,46 +1616,114 @@ __global__ __launch_bounds__(256) void k_stats_big_t(
       }
     }
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-#pragma unroll
-      for (int q = 0; q < DT; ++q)
-        acc[q] += (int64_t)__shfl_xor((long long)acc[q], off, kWave);
-      size += __shfl_xor(size, off, kWave);
-      cap += __shfl_xor(cap, off, kWave);
+    for (int off = kWave / 2; off > 0; off >>= 1)
       mp = min(mp, __shfl_xor(mp, off, kWave));
+    size = wave_sum(size);
+    cap = wave_sum(cap);
+#pragma unroll
+    for (int q = 0; q < DT; ++q) {
+      const long long r = wave_sum((long long)acc[q]);
+      if (lane == 0) sS[wv][q] = r;
     }
     if (lane == 0) {
-#pragma unroll
-      for (int q = 0; q < DT; ++q) sS[wv][q] = (long long)acc[q];
       ssize[wv] = size;
       smp[wv] = mp;
       scap[wv] = cap;
     }
     __syncthreads();
-    int32_t tsize = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) tsize += ssize[w];
+  };
+  // component c from its totals (thread 0 has the scalars, threads below DT
+  // a dimension each)
+  auto write = [&](int32_t c, int32_t members, long long v, int32_t size,
+                   int32_t mp, int32_t cap) {
     if (threadIdx.x == 0) {
-      int32_t tmp = INT32_MAX, tcap = 0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        tmp = min(tmp, smp[w]);
-        tcap += scap[w];
-      }
-      o.size[c] = tsize;
-      o.minpt[c] = tmp;
-      note_window(o, c, tcap, m1 - m0, ctl);
+      o.size[c] = size;
+      o.minpt[c] = mp;
+      note_window(o, c, cap, members, ctl);
     }
     if (threadIdx.x < DT) {
-      long long v = 0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) v += sS[w][threadIdx.x];
       const int64_t t = (int64_t)c * DT + threadIdx.x;
       o.S[t] = v;
-      const double qv = (double)v / (double)tsize;
+      const double qv = (double)v / (double)size;
       o.mu[t] = qv * sIF;
     }
+  };
+  auto totals = [&](long long &v, int32_t &size, int32_t &mp, int32_t &cap) {
+    v = 0;
+    size = cap = 0;
+    mp = INT32_MAX;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (threadIdx.x < DT) v += sS[w][threadIdx.x];
+      size += ssize[w];
+      cap += scap[w];
+      mp = min(mp, smp[w]);
+    }
+  };
+  for (int32_t bi = blockIdx.x; bi < n_big; bi += gridDim.x) {
+    const int32_t c = big[bi];
+    const int32_t m0 = moff[c], m1 = moff[c + 1];
+    if (m1 - m0 > kGiantMembers && bi < gslots) continue;
+    sum_members(m0, m1);
+    long long v;
+    int32_t size, mp, cap;
+    totals(v, size, mp, cap);
+    write(c, m1 - m0, v, size, mp, cap);
     __syncthreads();  // the shared sums are reused by the next component
+  }
+  const int32_t listed = min(n_big, gslots);
+  for (int32_t b0 = 0; b0 < listed; b0 += 256) {
+    __syncthreads();
+    if (threadIdx.x == 0) n_giant = 0;
+    __syncthreads();
+    const int32_t bi = b0 + (int32_t)threadIdx.x;
+    if (bi < listed && moff[big[bi] + 1] - moff[big[bi]] > kGiantMembers)
+      giant[atomicAdd(&n_giant, 1)] = bi;
+    __syncthreads();
+    for (int32_t g = 0; g < n_giant; ++g) {
+      const int32_t c = big[giant[g]];
+      const int32_t m0 = moff[c], m1 = moff[c + 1];
+      const int32_t nseg = (m1 - m0 + kGiantSeg - 1) / kGiantSeg;
+      unsigned long long *sum = gsum + (int64_t)giant[g] * kGiantStride;
+      // giants start at different blocks, so that their segments spread
+      const int32_t b1 = (int32_t)((blockIdx.x + gridDim.x -
+                                    (uint32_t)giant[g] % gridDim.x) %
+                                   gridDim.x);
+      for (int32_t q = b1; q < nseg; q += gridDim.x) {
+        const int32_t s0 = m0 + q * kGiantSeg;
+        sum_members(s0, min(s0 + kGiantSeg, m1));
+        long long v;
+        int32_t size, mp, cap;
+        totals(v, size, mp, cap);
+        if (threadIdx.x < DT) atomicAdd(&sum[threadIdx.x], (unsigned long long)v);
+        if (threadIdx.x == 0) {
+          atomicAdd(&sum[64], (unsigned long long)size);
+          atomicAdd(&sum[65], (unsigned long long)cap);
+          atomicMax(&sum[66], (unsigned long long)(INT32_MAX - mp));
+        }
+        __threadfence();  // the sums before the ticket
+        __syncthreads();
+        if (threadIdx.x == 0)
+          last = atomicAdd(&sum[67], 1ull) + 1 == (unsigned long long)nseg;
+        __syncthreads();
+        if (!last) continue;
+        __threadfence();  // every segment's sums after its ticket
+        auto take = [&](int i) {  // and zero again for the next round
+          return __hip_atomic_exchange(&sum[i], 0ull, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        };
+        if (threadIdx.x < DT) v = (long long)take(threadIdx.x);
+        if (threadIdx.x == 0) {
+          ssize[0] = (int32_t)take(64);
+          scap[0] = (int32_t)take(65);
+          smp[0] = INT32_MAX - (int32_t)take(66);
+          take(67);
+        }
+        __syncthreads();
+        write(c, m1 - m0, v, ssize[0], smp[0], scap[0]);
+        __syncthreads();
+      }
+    }
   }
 }
 
@@ -4302,6 +4395,8 @@ struct Bufs {
   double *lvl_mu;
   int32_t *bsum, *tmp;
   double *partial;
+  unsigned long long *gsum;  // giant components' partial sums
+  int32_t gslots;
   // linking of isolated nodes (only with the flag)
   bool link;
   const float4 *pts;  // points in internal order (linking only)
@@ -4391,6 +4486,9 @@ void carve(Arena &a, int32_t n, int32_t d, int32_t k, bool link, Bufs *b) {
   b->bsum = a.take<int32_t>(scan_blocks(ed + n1) + 2);
   b->tmp = a.take<int32_t>(8);
   b->partial = a.take<double>(kTailLevels * kEnergyBlocks);
+  // no more big components than n / kBigComp
+  b->gslots = std::min(kGiantSlots, n / kBigComp + 1);
+  b->gsum = a.take<unsigned long long>((size_t)b->gslots * kGiantStride);
   b->link = link;
   b->pts = nullptr;
   b->lk_sx[0] = b->lk_sx[1] = nullptr;
@@ -4512,7 +4610,8 @@ void launch_round(const Bufs &b, const Adj &adj, int cur, int32_t n,
   }
   if constexpr (DT > 0)
     hipLaunchKernelGGL((k_stats_big_t<FIRST, DT>), big_grid, dim3(256), 0, st,
-                       b.mem, b.moff, s, b.deg, o, b.big, ctl);
+                       b.mem, b.moff, s, b.deg, o, b.big, b.gsum, b.gslots,
+                       ctl);
   else
     hipLaunchKernelGGL(k_stats_big<FIRST>, big_grid, dim3(256), 0, st,
                      b.mem, b.moff, s, b.deg, d, o, b.big, ctl);
@@ -5116,10 +5215,9 @@ int ladder_run(const LadderArgs &g, Ctl *ctl, Arena &a, hipStream_t st) {
                        k, b.nbr_clean, ctl);
     nbr = b.nbr_clean;
   }
-  hipLaunchKernelGGL(k_fill_i32, blocks_for(n), dim3(256), 0, st, b.rev,
-                     (int64_t)n, 0);
-  hipLaunchKernelGGL(k_fill_i32, blocks_for(n), dim3(256), 0, st, b.cursor,
-                     (int64_t)n, 0);
+  hipLaunchKernelGGL(k_start_zero, blocks_for(n), dim3(256), 0, st, b.rev,
+                     b.cursor, (int64_t)n, b.gsum,
+                     (int64_t)b.gslots * kGiantStride);
   const bool blk = g.kth && g.pts;  // block-local count and fill
   const dim3 rev_grid(xcd_grid(((int64_t)n + kRevR - 1) / kRevR));
   if (blk)

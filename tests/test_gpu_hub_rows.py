@@ -56,3 +56,37 @@ def test_hub_rows(hub, noise, tail_mode):
     ref, rnc, _, _ = oracle.partition_graph(emb, lo, hi, w, lambdas)
     assert np.array_equal(nc, rnc)
     assert np.array_equal(labels.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("sizes", [(128, 129, 4096, 4097), (5000, 5121, 6144),
+                                   (70_000, 4097, 300)])
+def test_giant_components(sizes, tail_mode):
+    # components that absorb `sizes` points in one round: a block each, shared
+    # by blocks, ragged last segments; then merges among and into them
+    rng = np.random.default_rng(sum(sizes))
+    d = 16
+    n = sum(sizes) + 3000
+    nbr = np.full((n, 3), -1, np.int32)
+    emb = (rng.standard_normal((n, d)) * 3).astype(np.float32)
+    a = 0
+    for m in sizes:
+        nbr[a + 1:a + m, 0] = a  # a star around one point
+        emb[a:a + m] = (rng.standard_normal(d) * 2 +
+                        0.01 * rng.standard_normal((m, d))).astype(np.float32)
+        a += m
+    nbr[a:, 0] = rng.integers(0, n, n - a)
+    nbr[:, 1] = np.where(rng.random(n) < 0.1, rng.integers(0, n, n), -1)
+    order = rng.permutation(n)
+    table = np.full_like(nbr, -1)
+    table[order] = np.where(nbr >= 0, order[nbr], -1)
+    e = np.empty_like(emb)
+    e[order] = emb
+    lambdas = [0.5, 8.0, 60.0]
+    labels, nc, en = ezsp.partition_from_knn(
+        torch.from_numpy(table).cuda(), torch.from_numpy(e).cuda(), lambdas,
+        energy=True)
+    lo, hi, w = oracle.graph(table)
+    ref, rnc, ren, _ = oracle.partition_graph(e, lo, hi, w, lambdas)
+    assert np.array_equal(nc, rnc)
+    assert np.array_equal(labels.cpu().numpy(), ref)
+    np.testing.assert_allclose(en, ren, rtol=1e-9)
