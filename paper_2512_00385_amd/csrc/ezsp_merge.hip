@@ -2149,22 +2149,27 @@ __device__ __forceinline__ bool table_add(uint64_t *tbl, int32_t base,
   return false;
 }
 
+struct WideLds {
+  int32_t pk[kPreSlots];
+  int32_t pw[kPreSlots];
+  int32_t pre[kBatch + 1];
+  int32_t bm[kBatch];
+  int32_t wsum[256 / kWave];
+};
+
 template <bool FIRST>
-__global__ __launch_bounds__(256) void k_contract_big(
-    int32_t nn, Adj a, const int32_t *__restrict__ L,
-    const int32_t *__restrict__ mem, const int32_t *__restrict__ moff,
-    const int32_t *__restrict__ toff, const int32_t *__restrict__ cap,
-    const int32_t *__restrict__ tile_c, const int32_t *__restrict__ tile_i,
-    uint64_t *tbl, int32_t tcap, Ctl *ctl) {
-  __shared__ int32_t pk[kPreSlots];
-  __shared__ int32_t pw[kPreSlots];
-  __shared__ int32_t pre[kBatch + 1];
-  __shared__ int32_t bm[kBatch];
-  __shared__ int32_t wsum[256 / kWave];
-  if (!round_live(ctl)) return;
+__device__ __forceinline__ void contract_big(
+    WideLds &sh, int32_t block, int32_t blocks, int32_t nn, const Adj &a,
+    const int32_t *__restrict__ L, const int32_t *__restrict__ mem,
+    const int32_t *__restrict__ moff, const int32_t *__restrict__ toff,
+    const int32_t *__restrict__ cap, const int32_t *__restrict__ tile_c,
+    const int32_t *__restrict__ tile_i, uint64_t *tbl, int32_t tcap,
+    Ctl *ctl) {
+  int32_t *pk = sh.pk, *pw = sh.pw, *pre = sh.pre, *bm = sh.bm,
+          *wsum = sh.wsum;
   const int32_t n_tiles = ctl->n_tiles;
   int32_t added = 0;
-  for (int32_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+  for (int32_t t = block; t < n_tiles; t += blocks) {
     const int32_t A = tile_c[t];
     for (int q = threadIdx.x; q < kPreSlots; q += blockDim.x) {
       pk[q] = -1;
@@ -2232,17 +2237,16 @@ __global__ __launch_bounds__(256) void k_contract_big(
 // chunk: a block per chunk item, pre-aggregated in LDS (a chunk has fewer
 // entries than the LDS table has slots), then added to the window.
 template <bool FIRST>
-__global__ __launch_bounds__(256) void k_contract_long(
-    int32_t nn, Adj a, const int32_t *__restrict__ L,
-    const int32_t *__restrict__ toff, const int32_t *__restrict__ cap,
-    int32_t chunk, LongWork lw, uint64_t *tbl, int32_t tcap, Ctl *ctl) {
+__device__ __forceinline__ void contract_long(
+    WideLds &sh, int32_t block, int32_t blocks, int32_t nn, const Adj &a,
+    const int32_t *__restrict__ L, const int32_t *__restrict__ toff,
+    const int32_t *__restrict__ cap, int32_t chunk, const LongWork &lw,
+    uint64_t *tbl, int32_t tcap, Ctl *ctl) {
   static_assert(kLongChunk <= kPreSlots / 2, "a chunk fits the LDS table");
-  __shared__ int32_t pk[kPreSlots];
-  __shared__ int32_t pw[kPreSlots];
-  if (!round_live(ctl)) return;
+  int32_t *pk = sh.pk, *pw = sh.pw;
   const int32_t n_items = ctl->n_lchunk;
   int32_t added = 0;
-  for (int32_t it = blockIdx.x; it < n_items; it += gridDim.x) {
+  for (int32_t it = block; it < n_items; it += blocks) {
     const int32_t slot = lw.item[it];
     const int32_t v = lw.rows[slot];
     const int32_t A = L[v];
@@ -2288,6 +2292,27 @@ __global__ __launch_bounds__(256) void k_contract_long(
   added = wave_sum(added);
   if ((threadIdx.x & (kWave - 1)) == 0 && added)
     stripe_add(ctl->e_next_s, added);
+}
+
+// Both in one launch: the first `big_blocks` blocks take the member tiles of
+// the large windows, the others the chunks of long rows.  They write the same
+// windows with atomics only, so neither waits for the other.
+template <bool FIRST>
+__global__ __launch_bounds__(256) void k_contract_wide(
+    int32_t big_blocks, int32_t nn, Adj a, const int32_t *__restrict__ L,
+    const int32_t *__restrict__ mem, const int32_t *__restrict__ moff,
+    const int32_t *__restrict__ toff, const int32_t *__restrict__ cap,
+    const int32_t *__restrict__ tile_c, const int32_t *__restrict__ tile_i,
+    int32_t chunk, LongWork lw, uint64_t *tbl, int32_t tcap, Ctl *ctl) {
+  __shared__ WideLds sh;
+  if (!round_live(ctl)) return;
+  const int32_t b = (int32_t)blockIdx.x;
+  if (b < big_blocks)
+    contract_big<FIRST>(sh, b, big_blocks, nn, a, L, mem, moff, toff, cap,
+                        tile_c, tile_i, tbl, tcap, ctl);
+  else
+    contract_long<FIRST>(sh, b - big_blocks, (int32_t)gridDim.x - big_blocks,
+                         nn, a, L, toff, cap, chunk, lw, tbl, tcap, ctl);
 }
 
 // point -> node map after the first round (internal point i -> node L[i])
@@ -4516,6 +4541,8 @@ inline dim3 blocks_for(int64_t n, int nt = 256) {
   if (b < 1) b = 1;
   return dim3((unsigned)b);
 }
+constexpr int32_t kMapSync = 1 << 21;  // node maps worth bringing up to date
+
 inline dim3 xblocks_for(int64_t n) { return dim3(xcd_grid(blocks_for(n).x)); }
 
 
@@ -4635,12 +4662,10 @@ void launch_round(const Bufs &b, const Adj &adj, int cur, int32_t n,
                      dim3(xcd_grid((ed + chunk - 1) / chunk)), dim3(256), 0,
                      st, nn, adj, b.L, b.mem, b.moff, b.ws[nxt], b.capn,
                      b.cstart, b.tbl[nxt], b.wl[nxt], chunk, ctl);
-  hipLaunchKernelGGL(k_contract_big<FIRST>, big_grid, dim3(256), 0, st, nn,
-                     adj, b.L, b.mem, b.moff, b.ws[nxt], b.capn, b.tile_c,
-                     b.tile_i, b.tbl[nxt], tcap, ctl);
-  hipLaunchKernelGGL(k_contract_long<FIRST>, long_grid, dim3(256), 0, st, nn,
-                     adj, b.L, b.ws[nxt], b.capn, chunk, lw, b.tbl[nxt], tcap,
-                     ctl);
+  hipLaunchKernelGGL(k_contract_wide<FIRST>, dim3(big_grid.x + long_grid.x),
+                     dim3(256), 0, st, (int32_t)big_grid.x, nn, adj, b.L,
+                     b.mem, b.moff, b.ws[nxt], b.capn, b.tile_c, b.tile_i,
+                     chunk, lw, b.tbl[nxt], tcap, ctl);
   prof_end(st);
   if (b.link) {  // the next round's empty rows, read back with the round
     prof_begin("link", st);
@@ -5422,6 +5447,10 @@ int ladder_run(const LadderArgs &g, Ctl *ctl, Arena &a, hipStream_t st) {
       }
       const int32_t nn_before = nn;
       if (!first && mn == 0) mn = nn;  // the node map now spans this graph
+      // a map of many more nodes than are left is composed through all of
+      // them every round (25 us at 9.7M): into the point map once, and the
+      // next rounds compose a small one
+      if (mn >= kMapSync && h->n_next < mn / 8) sync_map(b, n, mn, ctl, st);
       cur = 1 - cur;
       first = false;
       slots = h->slots;
