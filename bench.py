@@ -609,7 +609,7 @@ def main():
     if dom == "knn_query" and not args.no_walk:
         # the kNN's walk, from its counting instantiation, after the timed
         # steps: buckets of 16 candidates scanned and inner nodes entered
-        # per 16-point query group
+        # per group of 64 query points
         _, scans, nodes = ezsp.knn_walk_stats(xyz, sc.k)
         scans = scans.double()
         out["knn_walk"] = {

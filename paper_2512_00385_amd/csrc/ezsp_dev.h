@@ -71,7 +71,7 @@ struct Ctl {
   Stripe e_fwd_s[kStripes];   // device side of e_fwd
   Stripe maxabs_s[kStripes];  // max |e| bits from the fused gather
   Stripe bbox_s[6][kStripes]; // bbox_enc's min xyz, max xyz per stripe
-                              // (folded into bbox_enc by k_bbox_fold)
+                              // (folded by each reader, fold_box)
   int32_t tail_nc[16];        // superpoints of every level the tail ended
   int64_t tail_cut2[16];      // 2 x the cut weight of every level
   double lvl_fid[16];         // its fidelity term
