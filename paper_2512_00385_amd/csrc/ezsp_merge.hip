@@ -2102,7 +2102,9 @@ __global__ __launch_bounds__(256) void k_clear_big(
       raise_err(ctl, kErrInternal);
       return;
     }
-    for (int32_t t = first; t < cp; t += step) tbl[base + t] = kEmpty;
+    // unsigned: a step past the largest window stays in range
+    for (uint32_t t = first; t < (uint32_t)cp; t += step)
+      tbl[base + t] = kEmpty;
     for (int32_t q = (base >> shift) + 1 + first; q <= (base + cp) >> shift;
          q += step)
       cstart[q] = c + 1;

@@ -141,8 +141,8 @@ __global__ __launch_bounds__(kPuNT) void k_pu_rows(
   const int32_t wave = (int32_t)(blockIdx.x * (kPuNT / kWave) +
                                  threadIdx.x / kWave);
   const int32_t waves = (int32_t)(gridDim.x * (kPuNT / kWave));
-  for (int32_t c = wave; c < nc; c += waves) {
-    const uint32_t *row = table + (int64_t)c * n_cls;
+  for (int64_t c = wave; c < nc; c += waves) {
+    const uint32_t *row = table + c * n_cls;
     uint64_t best = 0;
     uint32_t size = 0;
 #pragma unroll 4
