@@ -326,7 +326,10 @@ __global__ void k_ctl_init(Ctl *ctl) {
     ctl->n_cbig = 0;
     ctl->n_tiles = 0;
     ctl->tail_level = -1;
-    for (int l = 0; l < 16; ++l) ctl->tail_cut2[l] = 0;
+    for (int l = 0; l < 16; ++l) {
+      ctl->tail_nc[l] = 0;  // a level the tail does not end has no nodes
+      ctl->tail_cut2[l] = 0;
+    }
     ctl->maxabs_x_bits = 0;
     ctl->Fx = 0;
     ctl->n_iso = 0;
