@@ -19,6 +19,8 @@
 // counts are exact integers, and one thread forms the mean of
 // IoU_c = TP / (gt + pred - TP) in class order, so the result is independent
 // of scheduling.
+#include <algorithm>
+
 #include "ezsp_internal.h"
 
 namespace ezsp {
@@ -340,7 +342,10 @@ int key_bits(int64_t nkeys) {  // bits of nkeys - 1, at least 1
 
 namespace {
 
-// Workspace of one call: the counter table, or the sort's buffers.
+// Workspace of one call: the counter table, or the sort's buffers in its
+// place.  Room for both, so that the size grows with each argument and a
+// workspace for the largest of them serves all smaller ones, whichever way
+// those are counted.
 struct PurityWork {
   int64_t entries;  // of the table; 0: sorted
   uint32_t *table;
@@ -355,21 +360,18 @@ struct PurityWork {
 PurityWork take_work(Arena &a, int32_t n, int32_t nc, int32_t n_cls) {
   PurityWork w = {};
   w.entries = table_entries(n, nc, n_cls);
-  if (w.entries) {
-    w.table = a.take<uint32_t>(((size_t)w.entries + 3) / 4 * 4);
-  } else {
-    const size_t start = a.off;
-    w.keys = a.take<uint64_t>(n);
-    w.keys2 = a.take<uint64_t>(n);
-    w.hist = a.take<int32_t>(radix_hist_ints(n));
-    w.bsum = a.take<int32_t>(scan_blocks(radix_hist_ints(n)) + 1);
-    w.total = a.take<int32_t>(4);
-    w.best = a.take<unsigned long long>(nc);
-    // never less than the largest table: a workspace for many components
-    // also serves fewer
-    const size_t most = 4 * (size_t)table_most(n) + 1024;
-    if (a.off - start < most) a.take<char>(most - (a.off - start));
-  }
+  w.table = a.take<uint32_t>(0);
+  const size_t start = a.off;
+  w.keys = a.take<uint64_t>(n);
+  w.keys2 = a.take<uint64_t>(n);
+  w.hist = a.take<int32_t>(radix_hist_ints(n));
+  w.bsum = a.take<int32_t>(scan_blocks(radix_hist_ints(n)) + 1);
+  w.total = a.take<int32_t>(4);
+  w.best = a.take<unsigned long long>(nc);
+  const int64_t pairs =
+      nc <= INT64_MAX / n_cls ? (int64_t)nc * n_cls : INT64_MAX;
+  const size_t table = 4 * (size_t)std::min(pairs, table_most(n)) + 16;
+  a.off = std::max(a.off, start + table);
   w.maj = a.take<int32_t>(nc);
   w.cnt = a.take<unsigned long long>(3 * (size_t)n_cls);
   w.iou = a.take<double>(n_cls);
