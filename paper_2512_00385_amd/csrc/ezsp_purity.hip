@@ -7,10 +7,12 @@
 //   - a table of component x class counters while it has at most eight
 //     entries a point: blocks count their points in an LDS hash and add each
 //     distinct pair once, so that a giant superpoint's pair takes one atomic
-//     a block.  One wave per component then reads its row for the majority,
-//     and the per-class counts come from the rows too.  3M points of a
-//     driving tile, 8,500 superpoints x 541 classes: 219 us sorted, 109 us
-//     counted.
+//     a block.  A wave per component, or a few lanes where there are at most
+//     64 classes, then reads its row for the majority, and the per-class
+//     counts come from the rows too.  3M points of a driving tile, 8,500
+//     superpoints x 541 classes: 219 us sorted, 109 us counted.
+//     Atomics on one 128-byte line take about 10 ns each, however many blocks
+//     send them: a small table and a short class list are kept in copies.
 //   - else a radix sort of the keys component * n_cls + class; each run of
 //     equal keys is one pair, found by a binary search from the run head,
 //     and a 64-bit atomicMax of (count, ~class) per component picks the
@@ -31,6 +33,9 @@ constexpr int kPuNT = 256;
 constexpr int kPuLdsCls = 2048;  // class histograms held in LDS up to here
 constexpr int kPuHash = 4096;    // LDS hash slots of a counting block
 constexpr int kPuShare = 2816;   // points a counting block takes (load 0.69)
+constexpr int kPuNarrow = 64;    // classes up to which a lane keeps one class
+constexpr int kPuCntCopies = 16;   // of their per-class counts
+constexpr int64_t kPuSpread = 1 << 16;  // entries a table's copies fill
 
 // Entries the counter table may have (32-bit keys); eight a point cost as
 // much to clear and read as one pass of the sort.
@@ -41,6 +46,16 @@ int64_t table_most(int64_t n) {
 // Its entries, 0 when the pairs are sorted instead.
 int64_t table_entries(int64_t n, int64_t nc, int64_t n_cls) {
   return nc <= table_most(n) / n_cls ? nc * n_cls : 0;
+}
+
+// Copies of a small table, so that 1,000 blocks do not add to the same few
+// lines (3M points, ten superpoints x 8 classes in random order: 371 us with
+// one table, 130 sorted, 68 with copies).  None while there are few
+// blocks: folding them is one more launch.
+int32_t table_copies(int64_t n, int64_t entries) {
+  const int64_t blocks = (n + kPuShare - 1) / kPuShare;
+  const int64_t c = std::min(kPuSpread / entries, blocks / 32);
+  return (int32_t)std::max<int64_t>(1, std::min<int64_t>(c, 64));
 }
 
 __global__ __launch_bounds__(kPuNT) void k_pu_zero(uint4 *__restrict__ table,
@@ -74,11 +89,12 @@ __device__ __forceinline__ void pair_add(uint32_t key, uint32_t c,
   atomicAdd(&table[key], c);
 }
 
-// Counts the pairs of kPuShare points.
+// Counts the pairs of kPuShare points in this block's copy of the table.
 __global__ __launch_bounds__(kPuNT) void k_pu_tally(
     const int32_t *__restrict__ label, const int32_t *__restrict__ cls,
-    int32_t n, int32_t nc, int32_t n_cls, uint32_t *__restrict__ table,
-    Ctl *ctl) {
+    int32_t n, int32_t nc, int32_t n_cls, uint32_t *__restrict__ tables,
+    int64_t entries, int32_t copies, Ctl *ctl) {
+  uint32_t *table = tables + (int64_t)(blockIdx.x % copies) * entries;
   static_assert(kPuHash == 4096, "pair_slot gives 12 bits");
   __shared__ uint32_t hkey[kPuHash], hcnt[kPuHash];
   for (int i = threadIdx.x; i < kPuHash; i += kPuNT) {
@@ -126,6 +142,76 @@ __global__ __launch_bounds__(kPuNT) void k_pu_tally(
   __syncthreads();
   for (int i = threadIdx.x; i < kPuHash; i += kPuNT)
     if (hcnt[i]) atomicAdd(&table[hkey[i]], hcnt[i]);
+}
+
+// The table's copies added into the first.
+__global__ __launch_bounds__(kPuNT) void k_pu_fold(
+    uint32_t *__restrict__ table, int64_t entries, int32_t copies) {
+  const int64_t i = blockIdx.x * (int64_t)kPuNT + threadIdx.x;
+  if (i >= entries) return;
+  uint32_t s = 0;
+#pragma unroll 8
+  for (int32_t q = 0; q < copies; ++q) s += table[q * entries + i];
+  table[i] = s;
+}
+
+// At most kPuNarrow classes: G lanes per component, lane y of them with class
+// y of every component they come to, so that the per-class counts are sums in
+// registers; two components in flight.  (With a wave per component 3M
+// components of 8 classes took 718 us in all, sorted 307, so 190.)
+template <int G>
+__global__ __launch_bounds__(kPuNT) void k_pu_rows_narrow(
+    const uint32_t *__restrict__ table, int32_t nc, int32_t n_cls,
+    int32_t *__restrict__ maj, unsigned long long *cnt) {
+  static_assert(G <= kPuNarrow && kPuNarrow == kWave, "a class a lane");
+  constexpr int U = 2;
+  __shared__ uint32_t h[3 * kPuNarrow];
+  if (threadIdx.x < 3 * kPuNarrow) h[threadIdx.x] = 0;
+  __syncthreads();
+  const int32_t y = threadIdx.x & (G - 1);
+  uint32_t tp = 0, gt = 0, pr = 0;
+  const int64_t step = (int64_t)gridDim.x * (kPuNT / G);
+  for (int64_t c0 = (int64_t)blockIdx.x * (kPuNT / G) + threadIdx.x / G;
+       c0 < nc; c0 += U * step) {
+    uint32_t x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t c = c0 + u * step;
+      x[u] = c < nc && y < n_cls ? table[c * n_cls + y] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t c = c0 + u * step;
+      uint64_t best =
+          x[u] ? ((uint64_t)x[u] << 32) | (0xffffffffu - (uint32_t)y) : 0u;
+      uint32_t size = x[u];
+#pragma unroll
+      for (int off = G / 2; off > 0; off >>= 1) {
+        const uint64_t o = __shfl_xor((unsigned long long)best, off, G);
+        best = o > best ? o : best;
+        size += __shfl_xor(size, off, G);
+      }
+      const int32_t by = best ? (int32_t)(0xffffffffu - (uint32_t)best) : -1;
+      gt += x[u];
+      if (y == by) {
+        tp += x[u];
+        pr += size;
+      }
+      if (y == 0 && c < nc) maj[c] = by;
+    }
+  }
+  if (y < n_cls) {
+    if (tp) atomicAdd(&h[y], tp);
+    if (gt) atomicAdd(&h[kPuNarrow + y], gt);
+    if (pr) atomicAdd(&h[2 * kPuNarrow + y], pr);
+  }
+  __syncthreads();
+  cnt += (size_t)(blockIdx.x % kPuCntCopies) * 3 * n_cls;
+  if (threadIdx.x < 3 * kPuNarrow) {
+    const int32_t q = threadIdx.x / kPuNarrow, i = threadIdx.x % kPuNarrow;
+    if (h[threadIdx.x])
+      atomicAdd(&cnt[q * n_cls + i], (unsigned long long)h[threadIdx.x]);
+  }
 }
 
 // A wave per component: its row's majority (-1 when empty), and the row's
@@ -278,8 +364,8 @@ __global__ __launch_bounds__(kPuNT) void k_pu_count(
 constexpr int kPuChunk = 4096;
 
 __global__ __launch_bounds__(kPuNT) void k_pu_final(
-    const unsigned long long *cnt, int32_t n_cls, int32_t n, double *iou,
-    Ctl *ctl) {
+    const unsigned long long *cnt, int32_t copies, int32_t n_cls, int32_t n,
+    double *iou, Ctl *ctl) {
   __shared__ double v[kPuChunk];
   __shared__ unsigned long long tps[kPuNT / kWave];
   __shared__ int32_t prs[kPuNT / kWave];
@@ -293,8 +379,14 @@ __global__ __launch_bounds__(kPuNT) void k_pu_final(
       double x = 0.0;
       if (i < len) {
         const int32_t c = base + i;
-        const unsigned long long tp = cnt[c], gt = cnt[n_cls + c],
-                                 pr = cnt[2 * n_cls + c];
+        unsigned long long tp = 0, gt = 0, pr = 0;
+#pragma unroll 4
+        for (int32_t q = 0; q < copies; ++q) {
+          const unsigned long long *part = cnt + (int64_t)q * 3 * n_cls;
+          tp += part[c];
+          gt += part[n_cls + c];
+          pr += part[2 * n_cls + c];
+        }
         tp_mine += tp;
         present += gt ? 1 : 0;
         if (gt) x = __ddiv_rn((double)tp, (double)(gt + pr - tp));
@@ -348,6 +440,8 @@ namespace {
 // those are counted.
 struct PurityWork {
   int64_t entries;  // of the table; 0: sorted
+  int32_t copies;   // of the table
+  int32_t cnt_copies;
   uint32_t *table;
   uint64_t *keys, *keys2;
   int32_t *hist, *bsum, *total;
@@ -360,6 +454,8 @@ struct PurityWork {
 PurityWork take_work(Arena &a, int32_t n, int32_t nc, int32_t n_cls) {
   PurityWork w = {};
   w.entries = table_entries(n, nc, n_cls);
+  w.copies = w.entries ? table_copies(n, w.entries) : 1;
+  w.cnt_copies = w.entries && n_cls <= kPuNarrow ? kPuCntCopies : 1;
   w.table = a.take<uint32_t>(0);
   const size_t start = a.off;
   w.keys = a.take<uint64_t>(n);
@@ -370,10 +466,12 @@ PurityWork take_work(Arena &a, int32_t n, int32_t nc, int32_t n_cls) {
   w.best = a.take<unsigned long long>(nc);
   const int64_t pairs =
       nc <= INT64_MAX / n_cls ? (int64_t)nc * n_cls : INT64_MAX;
-  const size_t table = 4 * (size_t)std::min(pairs, table_most(n)) + 16;
+  const size_t table =
+      4 * (size_t)std::max(std::min(pairs, table_most(n)), kPuSpread) + 16;
   a.off = std::max(a.off, start + table);
   w.maj = a.take<int32_t>(nc);
-  w.cnt = a.take<unsigned long long>(3 * (size_t)n_cls);
+  w.cnt = a.take<unsigned long long>(
+      3 * (size_t)std::max(n_cls, kPuCntCopies * kPuNarrow));
   w.iou = a.take<double>(n_cls);
   return w;
 }
@@ -398,10 +496,10 @@ int purity_run(const int32_t *labels, int32_t n, int32_t nc,
   }
   const int nt = kPuNT;
   const int64_t gb = ((int64_t)n + nt - 1) / nt;
-  const int64_t ncnt = 3 * (int64_t)n_cls;
+  const int64_t ncnt = 3 * (int64_t)n_cls * w.cnt_copies;
   prof_begin("purity", st);
   if (w.entries) {
-    const int64_t vecs = (w.entries + 3) / 4;
+    const int64_t vecs = (w.entries * w.copies + 3) / 4;
     const int64_t zb = ((vecs > ncnt ? vecs : ncnt) + nt - 1) / nt;
     hipLaunchKernelGGL(k_pu_zero, dim3((unsigned)(zb < 2048 ? zb : 2048)),
                        dim3(nt), 0, st, reinterpret_cast<uint4 *>(w.table),
@@ -409,15 +507,32 @@ int purity_run(const int32_t *labels, int32_t n, int32_t nc,
     hipLaunchKernelGGL(k_pu_tally,
                        dim3((unsigned)(((int64_t)n + kPuShare - 1) / kPuShare)),
                        dim3(nt), 0, st, labels, cls, n, nc, n_cls, w.table,
-                       ctl);
-    const int64_t rb = ((int64_t)nc + nt / kWave - 1) / (nt / kWave);
-    const dim3 rg((unsigned)(rb < 1024 ? rb : 1024));
-    if (n_cls <= kPuLdsCls)
-      hipLaunchKernelGGL(k_pu_rows<true>, rg, dim3(nt), 0, st, w.table, nc,
-                         n_cls, maj, w.cnt);
-    else
-      hipLaunchKernelGGL(k_pu_rows<false>, rg, dim3(nt), 0, st, w.table, nc,
-                         n_cls, maj, w.cnt);
+                       w.entries, w.copies, ctl);
+    if (w.copies > 1)
+      hipLaunchKernelGGL(k_pu_fold,
+                         dim3((unsigned)((w.entries + nt - 1) / nt)), dim3(nt),
+                         0, st, w.table, w.entries, w.copies);
+    if (n_cls <= kPuNarrow) {
+      const auto narrow = [&](auto kernel, int g) {
+        const int64_t rb = ((int64_t)nc * g + 2 * nt - 1) / (2 * nt);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(rb < 1024 ? rb : 1024)),
+                           dim3(nt), 0, st, w.table, nc, n_cls, maj, w.cnt);
+      };
+      if (n_cls <= 4) narrow(k_pu_rows_narrow<4>, 4);
+      else if (n_cls <= 8) narrow(k_pu_rows_narrow<8>, 8);
+      else if (n_cls <= 16) narrow(k_pu_rows_narrow<16>, 16);
+      else if (n_cls <= 32) narrow(k_pu_rows_narrow<32>, 32);
+      else narrow(k_pu_rows_narrow<64>, 64);
+    } else {
+      const int64_t rb = ((int64_t)nc + nt / kWave - 1) / (nt / kWave);
+      const dim3 rg((unsigned)(rb < 1024 ? rb : 1024));
+      if (n_cls <= kPuLdsCls)
+        hipLaunchKernelGGL(k_pu_rows<true>, rg, dim3(nt), 0, st, w.table, nc,
+                           n_cls, maj, w.cnt);
+      else
+        hipLaunchKernelGGL(k_pu_rows<false>, rg, dim3(nt), 0, st, w.table, nc,
+                           n_cls, maj, w.cnt);
+    }
   } else {
     hipLaunchKernelGGL(k_pu_keys, dim3(xcd_grid(gb)), dim3(nt), 0, st, labels,
                        cls, n, nc, n_cls, w.keys, ctl);
@@ -440,8 +555,8 @@ int purity_run(const int32_t *labels, int32_t n, int32_t nc,
       hipLaunchKernelGGL(k_pu_count<false>, dim3(cg), dim3(nt), 0, st, labels,
                          cls, n, nc, maj, n_cls, w.cnt);
   }
-  hipLaunchKernelGGL(k_pu_final, dim3(1), dim3(nt), 0, st, w.cnt, n_cls, n,
-                     iou_out, ctl);
+  hipLaunchKernelGGL(k_pu_final, dim3(1), dim3(nt), 0, st, w.cnt,
+                     w.cnt_copies, n_cls, n, iou_out, ctl);
   prof_end(st);
   prof_bytes("purity", 8.0 * n + 4.0 * nc + 8.0 * n_cls);
   int rc = read_ctl(ctl, hc, st);

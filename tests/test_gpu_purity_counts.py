@@ -52,3 +52,25 @@ def test_one_workspace_for_many_components():
                              None, None, ctypes.byref(out), ws.data_ptr(),
                              most, torch.cuda.current_stream().cuda_stream)
         assert rc == ezsp.OK and out.purity == 1.0 and out.n_present == 1
+
+
+@pytest.mark.parametrize("n_cls", [1, 2, 4, 5, 8, 9, 16, 17, 33, 64, 65])
+def test_narrow_rows(n_cls):
+    # few lanes a component: more components than the grid takes in one step,
+    # a last step partly filled, and empty components
+    rng = np.random.default_rng(n_cls)
+    n, nc = 300_000, min(280_001, 2_400_000 // n_cls)
+    label = rng.integers(0, nc, n).astype(np.int32)
+    cls = ((label * 7 + rng.integers(0, 3, n)) % n_cls).astype(np.int32)
+    check_purity(label, nc, cls, n_cls)
+
+
+@pytest.mark.parametrize("n", [2816 * 64 - 1, 2816 * 64, 1_000_003])
+@pytest.mark.parametrize("nc,n_cls", [(1, 1), (1, 541), (10, 8), (300, 20),
+                                      (500, 64), (511, 64), (513, 64),
+                                      (16, 2048), (20, 2049)])
+def test_small_tables_in_copies(n, nc, n_cls):
+    rng = np.random.default_rng(n + nc)
+    label = rng.integers(0, nc, n).astype(np.int32)
+    cls = rng.integers(0, n_cls, n).astype(np.int32)
+    check_purity(label, nc, cls, n_cls)
