@@ -128,16 +128,17 @@ __global__ __launch_bounds__(256) void k_bbox(const float *xyz, int32_t n,
   }
 }
 
-// Bits per axis of the Morton codes.  The order only has to keep neighbours
-// close, so that fewer points need fewer bits: a quarter of the points of a
-// scene lie twice as far apart.  13 bits beat 12, 14 and 16 at 3M and 10M
-// points (10 bits leave dozens of points a voxel near a sensor: kNN 4.1
-// instead of 2.5 ms at 3M); 9 and 11 bits sort in three passes at the sizes
-// where a pass is launches and latency.
+// Bits per axis of the Morton codes, at every size.  Voxels are a share of the
+// farthest extent, and one stray return far off makes that many times the
+// scene's: 9 bits up to 2^16 points and 11 up to 2^19, which sort in fewer
+// passes, left thousands of points a voxel then (whole kNN in us, 13 bits /
+// fewer: a terrain and one point a hundred extents off, 20,000 points
+// 196/402, 65,536 220/798, 500,000 692/1733; without that point 173/159,
+// 241/234, 437/459).  13 bits beat 12, 14 and 16 at 3M and 10M points (10 bits
+// leave dozens of points a voxel near a sensor: kNN 4.1 instead of 2.5 ms at
+// 3M).
 constexpr int kMortonBits = 13;
-inline int morton_bits(int32_t n) {
-  return n <= (1 << 16) ? 9 : (n <= (1 << 19) ? 11 : kMortonBits);
-}
+constexpr float kMortonMax = (float)((1 << kMortonBits) - 1);
 
 // 16 bits -> every third bit of 48 (only the low kMortonBits are set).
 __device__ __forceinline__ uint64_t spread3(uint32_t v) {
@@ -155,8 +156,7 @@ __device__ __forceinline__ uint64_t spread3(uint32_t v) {
 constexpr int kPackBits = 25;
 constexpr int kMortonPer = 4;  // points a thread: fewer blocks fold the box
 __global__ __launch_bounds__(256) void k_morton(const float *xyz, int32_t n,
-                                                int bits, const Ctl *ctl,
-                                                uint64_t *keys,
+                                                const Ctl *ctl, uint64_t *keys,
                                                 uint32_t *vals) {
   __shared__ int32_t box[6];
   fold_box(ctl, box);
@@ -166,8 +166,7 @@ __global__ __launch_bounds__(256) void k_morton(const float *xyz, int32_t n,
     lo[a] = ord2f(box[a]);
     ext = fmaxf(ext, ord2f(box[3 + a]) - lo[a]);
   }
-  const float most = (float)((1 << bits) - 1);
-  const float scale = (ext > 0.0f) ? most / ext : 0.0f;
+  const float scale = (ext > 0.0f) ? kMortonMax / ext : 0.0f;
 #pragma unroll
   for (int j = 0; j < kMortonPer; ++j) {
     const int32_t i = (blockIdx.x * kMortonPer + j) * 256 + threadIdx.x;
@@ -176,7 +175,7 @@ __global__ __launch_bounds__(256) void k_morton(const float *xyz, int32_t n,
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       float t = (xyz[3 * (int64_t)i + a] - lo[a]) * scale;
-      t = fminf(fmaxf(t, 0.0f), most);  // NaN maps to 0
+      t = fminf(fmaxf(t, 0.0f), kMortonMax);  // NaN maps to 0
       q[a] = (uint32_t)t;
     }
     const uint64_t code =
@@ -963,10 +962,10 @@ void knn_reserve(Arena &a, int32_t n, int32_t k, KnnWork *w) {
 
 // The largest input of the walk with a wave per bucket.  k = 10, whole kNN
 // in us, wide / narrow, room, street, aerial tile and sweep: 20,000 points
-// 161/104 229/164 253/168 185/142; 120,000 274/244 395/312 502/375 190/194;
-// 250,000 312/319 478/428 560/426 255/302; 500,000 392/462 488/536 642/522
-// 357/444.  Longer lists fill the chip sooner (their insertions are the
-// work): K = 24 ends at 2^15 points, 32 and 64 never gain.
+// 257/177 326/246 330/227 227/169; 120,000 414/339 515/395 459/354 271/268;
+// 262,144 463/424 642/463 565/499 485/478; 500,000 (a coarser order) 392/462
+// 488/536 642/522 357/444.  Longer lists fill the chip sooner (their
+// insertions are the work): K = 24 ends at 2^15 points, 32 and 64 never gain.
 constexpr int kNarrowK = 24;
 constexpr int32_t narrow_max(int K) {
   return K <= 16 ? 1 << 18 : (K <= kNarrowK ? 1 << 15 : 0);
@@ -990,16 +989,15 @@ static hipError_t knn_impl(const float *xyz, int32_t n, int32_t k, Ctl *ctl,
   // moves 8 bytes a key instead of 12
   const bool pack = n <= (1 << kPackBits);
   static_assert(3 * kMortonBits + kPackBits <= 64, "code and index in a key");
-  const int bits = morton_bits(n);
   hipLaunchKernelGGL(k_morton, dim3((gb + kMortonPer - 1) / kMortonPer),
-                     dim3(nt), 0, st, xyz, n, bits, ctl, s.keys,
+                     dim3(nt), 0, st, xyz, n, ctl, s.keys,
                      pack ? (uint32_t *)nullptr : s.vals);
   prof_begin("morton_sort", st);
   const bool alt =
-      pack ? radix_sort_keys(s.keys, s.keys2, n, kPackBits, 3 * bits,
+      pack ? radix_sort_keys(s.keys, s.keys2, n, kPackBits, 3 * kMortonBits,
                              s.hist, s.bsum, s.total, ctl, st)
            : radix_sort_pairs(s.keys, s.vals, s.keys2, s.vals2, n,
-                              3 * bits, s.hist, s.bsum, s.total, ctl,
+                              3 * kMortonBits, s.hist, s.bsum, s.total, ctl,
                               st);
   prof_end(st);
   const uint32_t *order = pack ? nullptr : (alt ? s.vals2 : s.vals);
