@@ -87,7 +87,8 @@ struct Ctl {
   uint64_t sel_mask;          // ... and which bits those are
   int64_t sel_rank;           // rank still wanted below the prefix
   uint32_t sel_cand;          // keys listed for the threshold
-  int32_t sel_dense;          // the sample goes through every row
+  int32_t sel_dense;          // the threshold's bin overflows the list
+  int32_t sel_large;          // the sample is guessed to be large
   unsigned long long le_edges, le_intra, le_keep;
   double le_loss;             // Eq. loss over the sample
   double pu_miou, pu_purity;

@@ -24,7 +24,8 @@
 // transcendental functions run once a slot and not once a lane.
 //
 // Passes (driving tile of 3M points, k = 8, D = 32, rho = 0.3):
-//   k_le_prep    the table packed with the classes, the gradient zeroed
+//   k_le_prep    the table packed with the classes, the gradient zeroed, and
+//                the share of inter pairs guessed from 16384 slots
 //   k_le_pairs   classification, distances, affinities, the inter pairs'
 //                loss and gradient, and a histogram of the intra pairs' words
 //   k_le_pick    the sample's size, and the histogram bin its threshold is in
@@ -33,10 +34,12 @@
 //   k_le_select  the threshold among the listed keys
 //   k_le_listed  the listed pairs up to the threshold
 // The embedding rows and the neighbours' table rows are gathered once; a
-// small sample's rows are gathered again.  When the sample is a large part of
-// the slots, or the threshold's bin overflows the list (equal words), the
-// host runs the radix select over all slots and a row-wise pass instead
-// (k_le_hist, k_le_digit, k_le_dense).
+// small sample's rows are gathered again.  Where the guess says that the
+// sample is a large part of the pairs, k_le_pairs only classifies, k_le_sample
+// only lists, and a second k_le_pairs gathers every row once the threshold is
+// known.  When the threshold's bin overflows the list (equal words), the host
+// runs the radix select over all slots and that second pass instead
+// (k_le_hist, k_le_digit).
 //
 // The row accumulates the gradient on its own side of every sampled pair it
 // lists in registers; the other end q gets its side from its own row when q
@@ -44,6 +47,8 @@
 // A slot's 16-bit status carries the pair type, whether it owns the pair,
 // whether the pair is mutual, and where row q lists p, so a mirror slot can
 // read the owner's random word.
+#include <algorithm>
+
 #include "ezsp_internal.h"
 
 namespace ezsp {
@@ -68,6 +73,14 @@ constexpr int kLeCopies = 4;      // copies of it (atomics on one address)
 constexpr int kLeList = 16384;    // listed keys the threshold is found among
 constexpr int kLeTile = 2048;     // slots per step of k_le_sample
 constexpr int kLeStage = 1024 + kLeTile;  // keys a block stages for the list
+constexpr int kLeGuess = 64;      // blocks that guess, a slot a thread
+constexpr unsigned kLeListed = 64;  // blocks that take the listed pairs
+// The share of the pairs that makes a guessed sample a large one, with a
+// gradient and without (a sampled pair is two gathers and no atomics then).
+// 1M points, k = 8, D = 32, whole call in us, pair by pair / through the rows:
+// a share of 0.055 760/763, 0.077 871/853, 0.5 1670/785; without a gradient
+// 0.21 497/504, 0.5 521/431.
+constexpr float kLeLarge = 0.06f, kLeLargePlain = 0.25f;
 
 // Word bits of the first histogram: about half the list's capacity of intra
 // pairs a bin, if every other slot owned one.
@@ -238,11 +251,43 @@ __device__ __forceinline__ void clear_arrays(float *grad, int64_t count,
   for (int64_t i = done + t; i < count; i += step) grad[i] = 0.0f;
 }
 
+// Whether the intra sample is guessed to be a large part of the pairs, from
+// the guess's counts of inter pairs and of all pairs per block.  The same in
+// every lane; whole waves only.
+__device__ __forceinline__ bool guessed_large(
+    const uint32_t *__restrict__ guess, double rho, bool grad) {
+  static_assert(kLeGuess == kWave, "a count a lane");
+  const int lane = threadIdx.x & (kWave - 1);
+  const float inter = (float)wave_sum(guess[lane]);
+  const float all = (float)wave_sum(guess[kLeGuess + lane]);
+  const float cap = (float)(rho / (1.0 - rho)) * inter;  // of the sample
+  return fminf(all - inter, cap) > (grad ? kLeLarge : kLeLargePlain) * all;
+}
+
+// guess: null, or counts of the first kLeGuess blocks' slots (guessed_large;
+// the grid has as many blocks then).
 __global__ __launch_bounds__(kLeNT) void k_le_prep(
     const int32_t *__restrict__ nbr, int32_t n, int32_t k,
     const int32_t *__restrict__ cls, int4 *__restrict__ table, float *grad,
-    int64_t count, uint32_t *hist, int32_t nh) {
+    int64_t count, uint32_t *hist, int32_t nh, uint32_t *__restrict__ guess) {
+  __shared__ uint32_t shu[kLeNT / kWave];
+  const bool guesses = guess && blockIdx.x < kLeGuess;  // block-uniform
+  int32_t gp = 0, gq = -1, gcp = 0, gcq = 0;
+  if (guesses) {
+    // a slot of each of as many equal ranges, not at a fixed place in it
+    const uint32_t i = blockIdx.x * kLeNT + threadIdx.x;
+    const uint32_t ns = (uint32_t)((int64_t)n * k);
+    const uint32_t range = max(ns / (kLeGuess * kLeNT), 1u);
+    const uint32_t s = i * range + ((i * 2654435761u) >> 8) % range;
+    gp = (int32_t)(s / (uint32_t)k);
+    gq = s < ns ? nbr[s] : -1;
+  }
   clear_arrays(grad, count, hist, nh);
+  const bool pair = gq >= 0 && gq < n && gq != gp;
+  if (pair) {
+    gcp = cls[gp];
+    gcq = cls[gq];
+  }
   // a thread four ints of a packed row
   const int32_t quads = packed_ints(k) / 4;
   const int64_t step = (int64_t)gridDim.x * kLeNT;
@@ -256,6 +301,13 @@ __global__ __launch_bounds__(kLeNT) void k_le_prep(
                          j + 2 < k ? row[j + 2] : -1,
                          j + 3 < k ? row[j + 3] : -1);
   }
+  if (!guesses) return;
+  const uint32_t inter = block_sum((uint32_t)(pair && gcp != gcq), shu);
+  const uint32_t all = block_sum((uint32_t)pair, shu);
+  if (threadIdx.x == 0) {
+    guess[blockIdx.x] = inter;
+    guess[kLeGuess + blockIdx.x] = all;
+  }
 }
 
 __global__ __launch_bounds__(kLeNT) void k_le_clear(uint32_t *hist,
@@ -263,36 +315,193 @@ __global__ __launch_bounds__(kLeNT) void k_le_clear(uint32_t *hist,
   clear_arrays(nullptr, 0, hist, nh);
 }
 
+__device__ __forceinline__ uint64_t draw_key(const uint32_t *word, int64_t s) {
+  return ((uint64_t)word[s] << 32) | (uint64_t)s;
+}
+
+// Loss and gradient of one sampled intra pair by its owner slot, both sides
+// by atomics; the term is returned in lane 0 of the group.
+template <int G, int V, int NV>
+__device__ __forceinline__ double take_pair(
+    const float *__restrict__ emb, int32_t d, const int32_t *__restrict__ nbr,
+    int32_t k, uint32_t s, float inv_tau, float *grad, uint8_t *sampled,
+    int lane, float *stage) {
+  const int64_t p = (int64_t)(s / (uint32_t)k);
+  const int64_t q = nbr[s];
+  RowPart<G, V, NV> a, b;
+  a.load(emb, p, d, lane, true);
+  b.load(emb, q, d, lane, true);
+  const float dist = sqrtf(squared(a, b));
+  const float x = dist * inv_tau;
+  const float coef = pair_coef(true, dist, x, inv_tau);
+  if (grad && coef != 0.0f) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c)
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        const float g = coef * (a.v[c][v] - b.v[c][v]);
+        a.v[c][v] = g;
+        b.v[c][v] = -g;
+      }
+    add_row(grad, p, d, lane, a, stage);
+    add_row(grad, q, d, lane, b, stage);
+  }
+  if (lane != 0) return 0.0;
+  if (sampled) sampled[s] = 1;
+  return (double)pair_term(true, x);
+}
+
+// The listed pairs up to the threshold, by the first kLeListed blocks; a
+// thread's terms are returned.
+template <int G, int V, int NV>
+__device__ __forceinline__ double take_listed(
+    const float *__restrict__ emb, int32_t d, const int32_t *__restrict__ nbr,
+    int32_t k, float tau, float *__restrict__ grad,
+    uint8_t *__restrict__ sampled, const uint64_t *__restrict__ list,
+    float *stage, const Ctl *ctl) {
+  double lsum = 0.0;
+  if (ctl->sel_mode == 2) {
+    const uint32_t nc = min(ctl->sel_cand, (uint32_t)kLeList);
+    const uint64_t thr = ctl->sel_prefix;
+    const float inv_tau = 1.0f / tau;
+    const int lane = threadIdx.x & (G - 1);
+    const uint32_t blocks = min(gridDim.x, kLeListed);
+    for (uint32_t i = (blockIdx.x * kLeNT + threadIdx.x) / G; i < nc;
+         i += blocks * (kLeNT / G))
+      if (list[i] <= thr)
+        lsum += take_pair<G, V, NV>(emb, d, nbr, k, (uint32_t)list[i], inv_tau,
+                                    grad, sampled, lane, stage);
+  }
+  return lsum;
+}
+
+// Status of slot (p, j) that lists q != p, 0 <= q < n.
+__device__ __forceinline__ uint32_t slot_status(const int4 *__restrict__ prow,
+                                                int4 pfirst,
+                                                const int4 *__restrict__ qrow,
+                                                int32_t k, int32_t p,
+                                                int32_t j, int32_t q) {
+  const int4 qfirst = qrow[0];
+  const int32_t jq = find_in_row(qrow, qfirst, k, p);
+  const int32_t jp = find_in_row(prow, pfirst, k, q);
+  if (jp != j) return kSlotNone;  // an earlier slot of row p lists q
+  uint32_t st = qfirst.x == pfirst.x ? kSlotIntra : kSlotInter;
+  if (p < q || jq < 0) st |= kSlotOwner;
+  if (jq >= 0) st |= kSlotMutual | (uint32_t)(jq << 8);
+  return st;
+}
+
+// The classification alone, a slot a thread: statuses, pair counts and the
+// block's histogram of the intra pairs' words.  False for an id out of range.
+__device__ __forceinline__ bool classify_slots(
+    int32_t n, const int32_t *__restrict__ nbr, int32_t k,
+    const int4 *__restrict__ table, const uint32_t *__restrict__ word,
+    int bits, uint16_t *__restrict__ status, uint32_t *h,
+    unsigned long long &edges, unsigned long long &intra) {
+  bool inside = true;
+  const int64_t ns = (int64_t)n * k, quads = packed_ints(k) / 4;
+  for (int64_t s = blockIdx.x * (int64_t)kLeNT + threadIdx.x; s < ns;
+       s += (int64_t)gridDim.x * kLeNT) {
+    const int32_t p = (int32_t)((uint32_t)s / (uint32_t)k);
+    const int32_t j = (int32_t)(s - (int64_t)p * k), q = nbr[s];
+    uint32_t st = kSlotNone;
+    if (q < -1 || q >= n) {
+      inside = false;
+    } else if (q >= 0 && q != p) {
+      const int4 *prow = table + p * quads;
+      st = slot_status(prow, prow[0], table + q * quads, k, p, j, q);
+    }
+    status[s] = (uint16_t)st;
+    if (st & kSlotOwner) {
+      ++edges;
+      if ((st & 3) == kSlotIntra) {
+        ++intra;
+        atomicAdd(&h[word[s] >> (32 - bits)], 1u);
+      }
+    }
+  }
+  return inside;
+}
+
 // Everything that needs every slot: see the head of the file.  Bound by its
 // gathers: a random-order cloud fetches an embedding row and a packed table
-// row per slot.
-template <int G, int V, int NV>
+// row per slot.  Where the sample is guessed to be large it only classifies.
+// DRAWN: statuses and the sample's threshold are known.  Where the sample is
+// guessed to be large this does the rest, a mirror slot reading its owner's
+// word, so that only one-sided pairs need atomics on the far row; else the
+// first blocks take the listed pairs up to the threshold.  When the list
+// overflowed it waits for another launch (rest), which in the second case
+// adds the whole intra sample.
+template <int G, int V, int NV, bool DRAWN>
 __global__ __launch_bounds__(kLeNT) void k_le_pairs(
+    bool rest, const uint32_t *__restrict__ guess, double rho,
     const float *__restrict__ emb, int32_t n, int32_t d,
     const int32_t *__restrict__ nbr, int32_t k,
     const int4 *__restrict__ table, const uint32_t *__restrict__ word,
-    float tau, bool take_all, int bits, uint16_t *__restrict__ status,
+    float tau, int bits, uint16_t *__restrict__ status,
     float *__restrict__ affinity, float *__restrict__ grad,
     uint8_t *__restrict__ sampled, uint32_t *__restrict__ hist,
     unsigned long long *__restrict__ part_edges,
     unsigned long long *__restrict__ part_intra,
-    double *__restrict__ part_loss, Ctl *ctl) {
+    const uint64_t *__restrict__ list, double *__restrict__ part_loss,
+    Ctl *ctl) {
   constexpr int kRows = kLeNT / G;  // rows per block and step
   constexpr int U = NV == 1 ? 4 : (NV == 2 ? 2 : 1);  // gathers in flight
-  __shared__ uint32_t h[1 << kLeBitsMax];
+  __shared__ uint32_t h[DRAWN ? 1 : 1 << kLeBitsMax];
   __shared__ double shd[kLeNT / kWave];
   __shared__ unsigned long long shu[kLeNT / kWave];
   __shared__ alignas(16) float stage[stage_floats<V>()];
+  const bool large = DRAWN ? ctl->sel_large != 0
+                           : guess && guessed_large(guess, rho, grad != nullptr);
+  if (DRAWN) {
+    const bool wait = !rest && ctl->sel_dense;
+    if (wait || (!rest && !large)) {
+      const double t = wait || blockIdx.x >= kLeListed
+                           ? 0.0
+                           : take_listed<G, V, NV>(emb, d, nbr, k, tau, grad,
+                                                   sampled, list, stage, ctl);
+      const double tl = block_sum(t, shd);
+      if (threadIdx.x == 0) part_loss[blockIdx.x] = tl;
+      return;
+    }
+  }
+  const bool take_all = !DRAWN && rho >= 1.0;
+  const int mode = DRAWN ? ctl->sel_mode : 0;
+  const uint64_t thr = DRAWN ? ctl->sel_prefix : 0;
   const int lane = threadIdx.x & (G - 1);
   const int shift0 = (int)(threadIdx.x & (kWave - 1) & ~(G - 1));
   const uint64_t gmask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1);
   const float inv_tau = 1.0f / tau;
-  for (int i = threadIdx.x; i < (1 << bits); i += kLeNT) h[i] = 0;
+  if (!DRAWN)
+    for (int i = threadIdx.x; i < (1 << bits); i += kLeNT) h[i] = 0;
   __syncthreads();
   unsigned long long edges = 0, intra = 0;
   double lsum = 0.0;
   bool finite = true, inside = true;
   const int64_t quads = packed_ints(k) / 4;
+  const auto finish = [&]() {
+    if (!finite) raise_err(ctl, kErrNonFinite);
+    if (!inside) raise_err(ctl, kErrBadIndex);
+    const double tl = block_sum(lsum, shd);
+    if (threadIdx.x == 0) part_loss[blockIdx.x] = tl;
+    if (DRAWN) return;
+    const unsigned long long te = block_sum(edges, shu);
+    const unsigned long long ti = block_sum(intra, shu);
+    if (threadIdx.x == 0) {
+      part_edges[blockIdx.x] = te;
+      part_intra[blockIdx.x] = ti;
+    }
+    if (take_all) return;
+    uint32_t *to = hist + ((size_t)(blockIdx.x % kLeCopies) << bits);
+    for (int i = threadIdx.x; i < (1 << bits); i += kLeNT)
+      if (h[i]) atomicAdd(&to[i], h[i]);
+  };
+  if (!DRAWN && large) {
+    inside = classify_slots(n, nbr, k, table, word, bits, status, h, edges,
+                            intra);
+    finish();
+    return;
+  }
   for (int64_t p = (int64_t)blockIdx.x * kRows + threadIdx.x / G; p < n;
        p += (int64_t)gridDim.x * kRows) {
     const int32_t *row = nbr + p * k;
@@ -306,7 +515,7 @@ __global__ __launch_bounds__(kLeNT) void k_le_pairs(
         acc.v[c][v] = 0.0f;
       }
     const int4 *prow = table + p * quads;
-    const int4 pfirst = prow[0];
+    const int4 pfirst = DRAWN ? make_int4(0, 0, 0, 0) : prow[0];
     bool any = false;
     for (int32_t r0 = 0; r0 < k; r0 += G) {
       // lane t classifies slot r0 + t
@@ -318,27 +527,31 @@ __global__ __launch_bounds__(kLeNT) void k_le_pairs(
         q = -1;
       }
       uint32_t st = kSlotNone;
-      if (q >= 0 && q != p) {
-        const int4 *qrow = table + q * quads;
-        const int4 qfirst = qrow[0];
-        const int32_t jq = find_in_row(qrow, qfirst, k, (int32_t)p);
-        const int32_t jp = find_in_row(prow, pfirst, k, q);
-        if (jp == j) {  // no earlier slot of row p lists q
-          st = qfirst.x == pfirst.x ? kSlotIntra : kSlotInter;
-          if (p < q || jq < 0) st |= kSlotOwner;
-          if (jq >= 0) st |= kSlotMutual | (uint32_t)(jq << 8);
-        }
+      if (DRAWN) {
+        st = slot ? status[p * k + j] : kSlotNone;
+      } else if (q >= 0 && q != p) {
+        st = slot_status(prow, pfirst, table + q * quads, k, (int32_t)p, j, q);
       }
       const bool owner = (st & kSlotOwner) != 0;
       const bool same = (st & 3) == kSlotIntra;
-      const bool take = (st & 3) == kSlotInter || (take_all && same);
-      edges += owner;
-      intra += owner && same;
-      if (!take_all && owner && same)
-        atomicAdd(&h[word[p * k + j] >> (32 - bits)], 1u);
+      bool take = (st & 3) == kSlotInter || (take_all && same);
+      if (DRAWN) {
+        take = take && large;
+        if (same)
+          take = mode == 1 ||
+                 (mode == 2 &&
+                  draw_key(word, owner ? p * k + j
+                                       : (int64_t)q * k + (st >> 8)) <= thr);
+      } else {
+        edges += owner;
+        intra += owner && same;
+        if (!take_all && owner && same)
+          atomicAdd(&h[word[p * k + j] >> (32 - bits)], 1u);
+      }
       const uint64_t takes = (__ballot(take) >> shift0) & gmask;
       const uint64_t ones = (__ballot(!(st & kSlotMutual)) >> shift0) & gmask;
       const uint64_t sames = (__ballot(same) >> shift0) & gmask;
+      if (DRAWN && !large && !takes) continue;
       // the distances of the G slots, U gathers in flight
       float mine = 0.0f;
       const int32_t jn = min(G, k - r0);
@@ -378,37 +591,27 @@ __global__ __launch_bounds__(kLeNT) void k_le_pairs(
         const float x = sqrtf(mine) * inv_tau;
         if (take && owner) lsum += (double)pair_term(same, x);
         const int64_t s = p * k + j;
-        status[s] = (uint16_t)st;
+        if (!DRAWN) status[s] = (uint16_t)st;
         if (affinity) affinity[s] = q >= 0 ? expf(-x) : 0.0f;
-        if (sampled) sampled[s] = (take && owner) ? 1 : 0;
+        if (sampled && (!DRAWN || large || take))
+          sampled[s] = (take && owner) ? 1 : 0;
       }
     }
     if (any) add_row(grad, p, d, lane, acc, stage);
   }
-  if (!finite) raise_err(ctl, kErrNonFinite);
-  if (!inside) raise_err(ctl, kErrBadIndex);
-  const unsigned long long te = block_sum(edges, shu);
-  const unsigned long long ti = block_sum(intra, shu);
-  const double tl = block_sum(lsum, shd);
-  if (threadIdx.x == 0) {
-    part_edges[blockIdx.x] = te;
-    part_intra[blockIdx.x] = ti;
-    part_loss[blockIdx.x] = tl;
-  }
-  if (take_all) return;
-  uint32_t *to = hist + ((size_t)(blockIdx.x % kLeCopies) << bits);
-  for (int i = threadIdx.x; i < (1 << bits); i += kLeNT)
-    if (h[i]) atomicAdd(&to[i], h[i]);
+  finish();
 }
 
 // The pair counts, the size of the intra sample, the histogram bin of its
 // largest kept key (sel_prefix) and that key's rank in the bin (sel_rank).
 // sel_mode: 0 no intra pair is kept, 1 all, 2 those up to a threshold.
+// sel_dense: the bin holds more keys than the list.  sel_large: the guess.
 constexpr int kLePickNT = 1024;
 
 __global__ __launch_bounds__(kLePickNT) void k_le_pick(
-    Ctl *ctl, const uint32_t *__restrict__ hist, int bits, double rho,
-    int64_t ns, const unsigned long long *__restrict__ part_edges,
+    Ctl *ctl, const uint32_t *__restrict__ guess, bool grad,
+    const uint32_t *__restrict__ hist, int bits, double rho,
+    const unsigned long long *__restrict__ part_edges,
     const unsigned long long *__restrict__ part_intra, int32_t nparts) {
   __shared__ unsigned long long sh[kLePickNT / kWave];
   __shared__ int64_t wsum[kLePickNT / kWave];
@@ -421,6 +624,7 @@ __global__ __launch_bounds__(kLePickNT) void k_le_pick(
   }
   const unsigned long long edges = block_sum(e, sh);
   const unsigned long long intra = block_sum(a, sh);
+  const bool large = guess && guessed_large(guess, rho, grad);
   if (threadIdx.x == 0) {
     const int64_t n_intra = (int64_t)intra;
     const int64_t n_inter = (int64_t)edges - n_intra;
@@ -437,8 +641,8 @@ __global__ __launch_bounds__(kLePickNT) void k_le_pick(
     const int mode = m == 0 ? 0 : (m == n_intra ? 1 : 2);
     search = mode == 2;
     ctl->sel_mode = mode;
-    // a sample of an eighth of the slots or more goes through the rows
-    ctl->sel_dense = rho < 1.0 && m > ns / 8;
+    ctl->sel_dense = 0;
+    ctl->sel_large = large;
     ctl->sel_prefix = mode == 1 ? ~0ull : 0ull;
     ctl->sel_rank = 0;
     ctl->sel_cand = 0;
@@ -467,45 +671,10 @@ __global__ __launch_bounds__(kLePickNT) void k_le_pick(
   }
 }
 
-// Loss and gradient of one sampled intra pair by its owner slot, both sides
-// by atomics; the term is returned in lane 0 of the group.
-template <int G, int V, int NV>
-__device__ __forceinline__ double take_pair(
-    const float *__restrict__ emb, int32_t d, const int32_t *__restrict__ nbr,
-    int32_t k, uint32_t s, float inv_tau, float *grad, uint8_t *sampled,
-    int lane, float *stage) {
-  const int64_t p = (int64_t)(s / (uint32_t)k);
-  const int64_t q = nbr[s];
-  RowPart<G, V, NV> a, b;
-  a.load(emb, p, d, lane, true);
-  b.load(emb, q, d, lane, true);
-  const float dist = sqrtf(squared(a, b));
-  const float x = dist * inv_tau;
-  const float coef = pair_coef(true, dist, x, inv_tau);
-  if (grad && coef != 0.0f) {
-#pragma unroll
-    for (int c = 0; c < NV; ++c)
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const float g = coef * (a.v[c][v] - b.v[c][v]);
-        a.v[c][v] = g;
-        b.v[c][v] = -g;
-      }
-    add_row(grad, p, d, lane, a, stage);
-    add_row(grad, q, d, lane, b, stage);
-  }
-  if (lane != 0) return 0.0;
-  if (sampled) sampled[s] = 1;
-  return (double)pair_term(true, x);
-}
-
-__device__ __forceinline__ uint64_t draw_key(const uint32_t *word, int64_t s) {
-  return ((uint64_t)word[s] << 32) | (uint64_t)s;
-}
-
 // The sampled intra pairs below the threshold's bin (all of them in mode 1),
 // found by streaming statuses and words; a block lists a tile's pairs in LDS
-// and its groups of lanes then share them out.  Keys in the bin are listed.
+// and its groups of lanes then share them out.  Keys in the bin are listed;
+// no more than that where the sample is guessed to be large.
 template <int G, int V, int NV>
 __global__ __launch_bounds__(kLeNT) void k_le_sample(
     const float *__restrict__ emb, int32_t d, const int32_t *__restrict__ nbr,
@@ -518,7 +687,9 @@ __global__ __launch_bounds__(kLeNT) void k_le_sample(
   __shared__ uint32_t n_sure, n_stage, at;
   __shared__ double shd[kLeNT / kWave];
   __shared__ alignas(16) float astage[stage_floats<V>()];
-  const bool idle = ctl->sel_dense != 0 || ctl->sel_mode == 0;
+  const bool large = ctl->sel_large != 0;
+  const bool idle = ctl->sel_dense != 0 || ctl->sel_mode == 0 ||
+                    (large && ctl->sel_mode != 2);
   if (idle) {
     if (threadIdx.x == 0) part_loss[blockIdx.x] = 0.0;
     return;
@@ -537,9 +708,10 @@ __global__ __launch_bounds__(kLeNT) void k_le_sample(
       if (s < ns && (status[s] & (3 | kSlotOwner)) == (kSlotIntra | kSlotOwner)) {
         const uint32_t w = word[s];
         const uint64_t b = w >> (32 - bits);
-        if (b < bin) sure[atomicAdd(&n_sure, 1u)] = (uint32_t)s;
-        else if (b == bin)
+        if (b == bin)
           stage[atomicAdd(&n_stage, 1u)] = ((uint64_t)w << 32) | (uint64_t)s;
+        else if (b < bin && !large)
+          sure[atomicAdd(&n_sure, 1u)] = (uint32_t)s;
       }
     }
     __syncthreads();
@@ -612,31 +784,6 @@ __global__ __launch_bounds__(kLePickNT) void k_le_select(
     if ((key[i] & s_mask) == s_prefix) ctl->sel_prefix = key[i];
 }
 
-// The listed pairs up to the threshold.
-template <int G, int V, int NV>
-__global__ __launch_bounds__(kLeNT) void k_le_listed(
-    const float *__restrict__ emb, int32_t d, const int32_t *__restrict__ nbr,
-    int32_t k, float tau, float *__restrict__ grad,
-    uint8_t *__restrict__ sampled, const uint64_t *__restrict__ list,
-    double *__restrict__ part_loss, const Ctl *ctl) {
-  __shared__ double shd[kLeNT / kWave];
-  __shared__ alignas(16) float stage[stage_floats<V>()];
-  double lsum = 0.0;
-  if (ctl->sel_dense == 0 && ctl->sel_mode == 2) {
-    const uint32_t nc = min(ctl->sel_cand, (uint32_t)kLeList);
-    const uint64_t thr = ctl->sel_prefix;
-    const float inv_tau = 1.0f / tau;
-    const int lane = threadIdx.x & (G - 1);
-    for (uint32_t i = (blockIdx.x * kLeNT + threadIdx.x) / G; i < nc;
-         i += gridDim.x * (kLeNT / G))
-      if (list[i] <= thr)
-        lsum += take_pair<G, V, NV>(emb, d, nbr, k, (uint32_t)list[i], inv_tau,
-                                    grad, sampled, lane, stage);
-  }
-  const double t = block_sum(lsum, shd);
-  if (threadIdx.x == 0) part_loss[blockIdx.x] = t;
-}
-
 __global__ __launch_bounds__(kLePickNT) void k_le_total(
     const double *__restrict__ part, int32_t nparts, Ctl *ctl) {
   __shared__ double sh[kLePickNT / kWave];
@@ -646,7 +793,7 @@ __global__ __launch_bounds__(kLePickNT) void k_le_total(
   if (threadIdx.x == 0) ctl->le_loss = s;
 }
 
-// --- the general selection: radix passes over every slot, then the rows ----
+// --- the general selection: radix passes over every slot ------------------
 
 __global__ void k_le_dense_start(Ctl *ctl) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
@@ -696,81 +843,6 @@ __global__ __launch_bounds__(256) void k_le_digit(Ctl *ctl, uint32_t *hist,
   }
 }
 
-// Loss and gradient of the sampled intra pairs, a group of lanes a row; a
-// mirror slot reads its owner's word, so that only one-sided pairs need
-// atomics on the far row.
-template <int G, int V, int NV>
-__global__ __launch_bounds__(kLeNT) void k_le_dense(
-    const float *__restrict__ emb, int32_t n, int32_t d,
-    const int32_t *__restrict__ nbr, int32_t k,
-    const uint16_t *__restrict__ status, const uint32_t *__restrict__ word,
-    float tau, float *__restrict__ grad, uint8_t *__restrict__ sampled,
-    double *__restrict__ part_loss, const Ctl *ctl) {
-  constexpr int kRows = kLeNT / G;
-  __shared__ double shd[kLeNT / kWave];
-  __shared__ alignas(16) float stage[stage_floats<V>()];
-  const int lane = threadIdx.x & (G - 1);
-  const int shift0 = (int)(threadIdx.x & (kWave - 1) & ~(G - 1));
-  const uint64_t gmask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1);
-  const bool all = ctl->sel_mode == 1;
-  const uint64_t thr = ctl->sel_prefix;
-  const float inv_tau = 1.0f / tau;
-  double lsum = 0.0;
-  for (int64_t p = (int64_t)blockIdx.x * kRows + threadIdx.x / G; p < n;
-       p += (int64_t)gridDim.x * kRows) {
-    RowPart<G, V, NV> ep, acc;
-    ep.load(emb, p, d, lane, true);
-#pragma unroll
-    for (int c = 0; c < NV; ++c)
-#pragma unroll
-      for (int v = 0; v < V; ++v) acc.v[c][v] = 0.0f;
-    bool any = false;
-    for (int32_t r0 = 0; r0 < k; r0 += G) {
-      const int32_t j = r0 + lane;
-      const int64_t s = p * k + j;
-      const uint32_t st = j < k ? status[s] : 0u;
-      const int32_t q = j < k ? nbr[s] : -1;
-      const bool owner = (st & kSlotOwner) != 0;
-      bool take = (st & 3) == kSlotIntra;
-      if (take && !all)
-        take = draw_key(word, owner ? s : (int64_t)q * k + (st >> 8)) <= thr;
-      uint64_t takes = (__ballot(take) >> shift0) & gmask;
-      const uint64_t ones = (__ballot(!(st & kSlotMutual)) >> shift0) & gmask;
-      float mine = 0.0f;
-      while (takes) {
-        const int u = __ffsll((unsigned long long)takes) - 1;
-        takes &= takes - 1;
-        const int32_t qu = __shfl(q, u, G);
-        RowPart<G, V, NV> eq;
-        eq.load(emb, qu, d, lane, true);
-        const float part = squared(ep, eq);
-        mine = lane == u ? part : mine;
-        if (!grad) continue;
-        const float dist = sqrtf(part);
-        const float coef = pair_coef(true, dist, dist * inv_tau, inv_tau);
-        any = true;
-#pragma unroll
-        for (int c = 0; c < NV; ++c)
-#pragma unroll
-          for (int v = 0; v < V; ++v) {
-            const float g = coef * (ep.v[c][v] - eq.v[c][v]);
-            acc.v[c][v] += g;
-            eq.v[c][v] = -g;
-          }
-        if (((ones >> u) & 1) && coef != 0.0f)
-          add_row(grad, qu, d, lane, eq, stage);
-      }
-      if (take && owner) {
-        lsum += (double)pair_term(true, sqrtf(mine) * inv_tau);
-        if (sampled) sampled[s] = 1;
-      }
-    }
-    if (any) add_row(grad, p, d, lane, acc, stage);
-  }
-  const double t = block_sum(lsum, shd);
-  if (threadIdx.x == 0) part_loss[blockIdx.x] = t;
-}
-
 unsigned grid_for(int64_t items) {
   const int64_t b = (items + kLeNT - 1) / kLeNT;
   return (unsigned)(b < kLeGrid ? (b < 1 ? 1 : b) : kLeGrid);
@@ -783,8 +855,9 @@ struct LossWork {
   uint32_t *hist;
   uint64_t *list;
   unsigned long long *part_edges, *part_intra;
-  double *part_loss;  // k_le_pairs, then k_le_sample or k_le_dense, then
-                      // k_le_listed: kLeGrid each
+  double *part_loss;  // of the first k_le_pairs, the second, and k_le_sample:
+                      // kLeGrid each
+  uint32_t *guess;
 };
 
 LossWork take_work(Arena &a, int32_t n, int32_t k) {
@@ -797,6 +870,7 @@ LossWork take_work(Arena &a, int32_t n, int32_t k) {
   w.part_edges = a.take<unsigned long long>(kLeGrid);
   w.part_intra = a.take<unsigned long long>(kLeGrid);
   w.part_loss = a.take<double>(3 * kLeGrid);
+  w.guess = a.take<uint32_t>(2 * kLeGuess);
   return w;
 }
 
@@ -805,37 +879,29 @@ template <int G, int V, int NV>
 struct Rows {
   static unsigned blocks(int64_t n) { return grid_for(n * G); }
 
-  static void pairs(const LossArgs &g, const LossWork &w, int bits, Ctl *ctl,
+  template <bool DRAWN>
+  static void pairs(const LossArgs &g, const LossWork &w,
+                    const uint32_t *guess, int bits, bool rest, Ctl *ctl,
                     hipStream_t st) {
-    hipLaunchKernelGGL((k_le_pairs<G, V, NV>), dim3(blocks(g.n)), dim3(kLeNT),
-                       0, st, g.emb, g.n, g.d, g.nbr, g.k, w.table, g.word,
-                       (float)g.tau, g.rho >= 1.0, bits, w.status, g.affinity,
-                       g.grad, g.sampled, w.hist, w.part_edges, w.part_intra,
-                       w.part_loss, ctl);
+    const unsigned pb = blocks(g.n);
+    hipLaunchKernelGGL((k_le_pairs<G, V, NV, DRAWN>), dim3(pb), dim3(kLeNT), 0,
+                       st, rest, guess, g.rho, g.emb, g.n, g.d, g.nbr, g.k,
+                       w.table, g.word, (float)g.tau, bits, w.status,
+                       g.affinity, g.grad, g.sampled, w.hist, w.part_edges,
+                       w.part_intra, w.list, w.part_loss + (DRAWN ? pb : 0),
+                       ctl);
   }
 
-  // the sample by list
+  // finding the sample's threshold, and with it its sure pairs
   static void sample(const LossArgs &g, const LossWork &w, int bits, Ctl *ctl,
-                     unsigned sb, unsigned lb, hipStream_t st) {
+                     unsigned sb, hipStream_t st) {
     const int64_t ns = (int64_t)g.n * g.k;
-    const unsigned pb = blocks(g.n);
     hipLaunchKernelGGL((k_le_sample<G, V, NV>), dim3(sb), dim3(kLeNT), 0, st,
-                       g.emb, g.d, g.nbr, g.k, w.status, g.word, ns,
-                       (float)g.tau, bits, g.grad, g.sampled, w.list,
-                       w.part_loss + pb, ctl);
+                       g.emb, g.d, g.nbr, g.k, w.status, g.word,
+                       ns, (float)g.tau, bits, g.grad, g.sampled, w.list,
+                       w.part_loss + 2 * blocks(g.n), ctl);
     hipLaunchKernelGGL(k_le_select, dim3(1), dim3(kLePickNT), 0, st, ctl,
                        w.list, bits);
-    hipLaunchKernelGGL((k_le_listed<G, V, NV>), dim3(lb), dim3(kLeNT), 0, st,
-                       g.emb, g.d, g.nbr, g.k, (float)g.tau, g.grad,
-                       g.sampled, w.list, w.part_loss + pb + sb, ctl);
-  }
-
-  static void dense(const LossArgs &g, const LossWork &w, Ctl *ctl,
-                    hipStream_t st) {
-    const unsigned pb = blocks(g.n);
-    hipLaunchKernelGGL((k_le_dense<G, V, NV>), dim3(pb), dim3(kLeNT), 0, st,
-                       g.emb, g.n, g.d, g.nbr, g.k, w.status, g.word,
-                       (float)g.tau, g.grad, g.sampled, w.part_loss + pb, ctl);
   }
 };
 
@@ -847,37 +913,39 @@ int run_rows(const LossArgs &g, const LossWork &w, Ctl *ctl, Ctl *hc,
   const unsigned pb = R::blocks(g.n);
   const int64_t tiles = (ns + kLeTile - 1) / kLeTile;
   const unsigned sb = (unsigned)(tiles < kLeGrid ? tiles : kLeGrid);
-  const unsigned lb = 64;
+  const bool draws = g.rho < 1.0;
+  uint32_t *guess = draws ? w.guess : nullptr;
   prof_begin("edge_loss", st);
-  const int64_t quads = (int64_t)g.n * (packed_ints(g.k) / 4);
-  hipLaunchKernelGGL(k_le_prep, dim3(grid_for(quads)), dim3(kLeNT), 0, st,
-                     g.nbr, g.n, g.k, g.cls, w.table, g.grad,
-                     (int64_t)g.n * g.d, w.hist, kLeCopies << bits);
-  R::pairs(g, w, bits, ctl, st);
-  hipLaunchKernelGGL(k_le_pick, dim3(1), dim3(kLePickNT), 0, st, ctl, w.hist,
-                     bits, g.rho, ns, w.part_edges, w.part_intra, (int32_t)pb);
-  unsigned parts = pb;
-  if (g.rho < 1.0) {
-    R::sample(g, w, bits, ctl, sb, lb, st);
-    parts += sb + lb;
+  const unsigned quads = grid_for((int64_t)g.n * (packed_ints(g.k) / 4));
+  hipLaunchKernelGGL(k_le_prep, dim3(std::max(quads, (unsigned)kLeGuess)),
+                     dim3(kLeNT), 0, st, g.nbr, g.n, g.k, g.cls, w.table,
+                     g.grad, (int64_t)g.n * g.d, w.hist, kLeCopies << bits,
+                     guess);
+  R::template pairs<false>(g, w, guess, bits, false, ctl, st);
+  hipLaunchKernelGGL(k_le_pick, dim3(1), dim3(kLePickNT), 0, st, ctl, guess,
+                     g.grad != nullptr, w.hist, bits, g.rho, w.part_edges, w.part_intra, (int32_t)pb);
+  if (draws) {
+    R::sample(g, w, bits, ctl, sb, st);
+    R::template pairs<true>(g, w, guess, bits, false, ctl, st);
   }
+  const int32_t parts = (int32_t)(draws ? 2 * pb + sb : pb);
   hipLaunchKernelGGL(k_le_total, dim3(1), dim3(kLePickNT), 0, st, w.part_loss,
-                     (int32_t)parts, ctl);
+                     parts, ctl);
   prof_end(st);
   int rc = read_ctl(ctl, hc, st);
   if (rc || hc->err || !hc->sel_dense) return rc;
   prof_begin("edge_loss", st);
   hipLaunchKernelGGL(k_le_dense_start, dim3(1), dim3(64), 0, st, ctl);
   hipLaunchKernelGGL(k_le_clear, dim3(1), dim3(kLeNT), 0, st, w.hist, 256);
-  for (int shift = 56; shift >= 0 && hc->sel_mode == 2; shift -= 8) {
+  for (int shift = 56; shift >= 0; shift -= 8) {
     hipLaunchKernelGGL(k_le_hist, dim3(grid_for(ns)), dim3(kLeNT), 0, st,
                        w.status, g.word, ns, shift, ctl, w.hist);
     hipLaunchKernelGGL(k_le_digit, dim3(1), dim3(256), 0, st, ctl, w.hist,
                        shift);
   }
-  R::dense(g, w, ctl, st);
+  R::template pairs<true>(g, w, guess, bits, true, ctl, st);
   hipLaunchKernelGGL(k_le_total, dim3(1), dim3(kLePickNT), 0, st, w.part_loss,
-                     (int32_t)(2 * pb), ctl);
+                     parts, ctl);
   prof_end(st);
   return read_ctl(ctl, hc, st);
 }

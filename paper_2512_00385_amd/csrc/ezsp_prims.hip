@@ -341,6 +341,7 @@ __global__ void k_ctl_init(Ctl *ctl) {
     ctl->sel_rank = 0;
     ctl->sel_cand = 0;
     ctl->sel_dense = 0;
+    ctl->sel_large = 0;
     ctl->le_edges = 0;
     ctl->le_intra = 0;
     ctl->le_keep = 0;
