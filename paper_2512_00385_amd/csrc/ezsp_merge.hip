@@ -2803,6 +2803,10 @@ __global__ __launch_bounds__(kTailNT) void k_tail(TailState t, Ctl *ctl) {
     if (threadIdx.x == 0) raise_err(ctl, kErrInternal);
     return;
   }
+  // an entry that k_repack refused left its slot unwritten, and the first
+  // round takes both ends of every slot as node ids (this kernel raises no
+  // error before its first barrier)
+  if (ctl->err) return;
   int32_t tc = t.tcur0;
   if (threadIdx.x < kTailLevels) {
     s_lambda[threadIdx.x] = t.lambda[threadIdx.x];
