@@ -822,7 +822,7 @@ __attribute__((amdgpu_waves_per_eu(narrow_waves(K)))) void k_knn_narrow(
   // own children with the k-th distances of then is as cheap as a test of
   // its box.  Leaves are scanned where their parent is entered, four loaded
   // ahead, and re-tested with the distances kept from the entry.
-  uint64_t mlo = 0, mhi = 0;
+  uint64_t pending = 0;
   int32_t node = 0, first = 0;
   int l = tree.top;   // the level of `node`
   bool down = false;  // the root has been entered
@@ -852,16 +852,9 @@ __attribute__((amdgpu_waves_per_eu(narrow_waves(K)))) void k_knn_narrow(
         down = true;
         if (tree.top == 0) break;
       } else {
-        int t;
-        if (mlo != 0) {
-          t = __builtin_ctzll(mlo);
-          mlo &= mlo - 1;
-        } else {
-          // levels 8 and up (trees over more than 8^8 buckets only)
-          if (mhi == 0) break;
-          t = 64 + __builtin_ctzll(mhi);
-          mhi &= mhi - 1;
-        }
+        if (pending == 0) break;
+        const int t = __builtin_ctzll(pending);
+        pending &= pending - 1;
         const int lt = t >> 3;
         node = ((node >> (3 * (lt + 1 - l))) << 3) | (t & 7);
         l = lt;
@@ -877,7 +870,7 @@ __attribute__((amdgpu_waves_per_eu(narrow_waves(K)))) void k_knn_narrow(
       left = (1u << nchild) - 1u;
       m8 = narrow_need(da, db, (uint32_t)(key[K - 1] >> 32), act) & left;
       if (lc > 0) {
-        set_level_bits(mlo, mhi, lc, m8);
+        pending |= (uint64_t)m8 << (kFan * lc);
         m8 = 0;
         continue;
       }
@@ -966,10 +959,9 @@ void knn_reserve(Arena &a, int32_t n, int32_t k, KnnWork *w) {
 // 262,144 463/424 642/463 565/499 485/478; 500,000 (a coarser order) 392/462
 // 488/536 642/522 357/444.  Longer lists fill the chip sooner (their
 // insertions are the work): K = 24 ends at 2^15 points, 32 and 64 never gain.
-constexpr int kNarrowK = 24;
-constexpr int32_t narrow_max(int K) {
-  return K <= 16 ? 1 << 18 : (K <= kNarrowK ? 1 << 15 : 0);
-}
+constexpr int32_t narrow_max(int K) { return K <= 16 ? 1 << 18 : 1 << 15; }
+static_assert(narrow_max(16) / kBucket <= 1 << 24 && kFan == 8,
+              "the narrow walk's pending children fit one word");
 
 // the largest level left to the single-block kernel
 constexpr int32_t kTopBoxes = 512;
@@ -1023,19 +1015,12 @@ static hipError_t knn_impl(const float *xyz, int32_t n, int32_t k, Ctl *ctl,
   float4 *emb_out4 = reinterpret_cast<float4 *>(emb_out);
   prof_begin("knn_query", st);
   switch (knn_template_k(k)) {
-#define EZSP_KNN_CASE(KK)                                                    \
-  case KK:                                                                   \
+#define EZSP_KNN_WIDE(KK)                                                    \
     if (st_scan)                                                             \
       hipLaunchKernelGGL((k_knn_query<KK, true>), grid, dim3(nt), 0, st,     \
                          s.pts, w.inv, n, s.blo, s.bhi, tree, k, w.nbr_int,  \
                          nbr_out, d2_out, w.kth, n_waves, emb4, d / 4,       \
                          emb_out4, ctl, st_scan, st_node);                   \
-    else if (n <= narrow_max(KK))                                            \
-      hipLaunchKernelGGL(k_knn_narrow<(KK <= kNarrowK ? KK : kNarrowK)>,     \
-                         dim3(xcd_grid((tree.cnt[0] + 3) / 4)), dim3(nt), 0, \
-                         st, s.pts, w.inv, n, s.blo, s.bhi, tree, k,         \
-                         w.nbr_int, nbr_out, d2_out, w.kth, emb4, d / 4,     \
-                         emb_out4, ctl);                                     \
     else                                                                     \
       hipLaunchKernelGGL(k_knn_query<KK>, grid, dim3(nt), 0, st, s.pts,      \
                          w.inv, n, s.blo, s.bhi, tree, k, w.nbr_int,         \
@@ -1043,14 +1028,25 @@ static hipError_t knn_impl(const float *xyz, int32_t n, int32_t k, Ctl *ctl,
                          emb_out4, ctl, (int32_t *)nullptr,                  \
                          (int32_t *)nullptr);                                \
     break;
-    EZSP_KNN_CASE(4)
-    EZSP_KNN_CASE(8)
-    EZSP_KNN_CASE(10)
-    EZSP_KNN_CASE(16)
-    EZSP_KNN_CASE(24)
-    EZSP_KNN_CASE(32)
-    EZSP_KNN_CASE(64)
-#undef EZSP_KNN_CASE
+#define EZSP_KNN_BOTH(KK)                                                    \
+    if (!st_scan && n <= narrow_max(KK)) {                                   \
+      hipLaunchKernelGGL(k_knn_narrow<KK>,                                   \
+                         dim3(xcd_grid((tree.cnt[0] + 3) / 4)), dim3(nt), 0, \
+                         st, s.pts, w.inv, n, s.blo, s.bhi, tree, k,         \
+                         w.nbr_int, nbr_out, d2_out, w.kth, emb4, d / 4,     \
+                         emb_out4, ctl);                                     \
+      break;                                                                 \
+    }                                                                        \
+    EZSP_KNN_WIDE(KK)
+    case 4: EZSP_KNN_BOTH(4)
+    case 8: EZSP_KNN_BOTH(8)
+    case 10: EZSP_KNN_BOTH(10)
+    case 16: EZSP_KNN_BOTH(16)
+    case 24: EZSP_KNN_BOTH(24)
+    case 32: EZSP_KNN_WIDE(32)
+    case 64: EZSP_KNN_WIDE(64)
+#undef EZSP_KNN_BOTH
+#undef EZSP_KNN_WIDE
     default:
       prof_end(st);
       return hipErrorInvalidValue;

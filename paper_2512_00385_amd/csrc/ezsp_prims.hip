@@ -248,48 +248,34 @@ void sort_pass(const SortBufs &b, int32_t n, int shift, int db, Ctl *ctl,
                      db, b.hist, nb, ctl);
 }
 
-template <bool VALS>
-bool sort_run(SortBufs b, int32_t n, int shift0, int nbits, Ctl *ctl,
-              hipStream_t st) {
+// The passes, of digits of at most DB bits; true when the sorted result
+// ended in the *out buffers.
+template <bool VALS, int DB, int NT, int ITEMS, bool SUM>
+bool sort_passes(SortBufs b, int32_t n, int shift0, int nbits, Ctl *ctl,
+                 hipStream_t st) {
   if (n <= 1 || nbits <= 0) return false;
-  const int most = n <= kSmallMax ? kSmallBits
-                   : n <= kMidMax ? kMidBits
-                   : n <= kBigMax ? kBigBits
-                                  : kHugeBits;
-  const int passes = (nbits + most - 1) / most;
-  bool flip = false;
+  const int passes = (nbits + DB - 1) / DB;
   int shift = shift0;
   for (int q = 0; q < passes; ++q) {
     // the bits left over the passes left, so digits differ by a bit at most
     const int left = shift0 + nbits - shift;
     const int db = (left + passes - q - 1) / (passes - q);
-    if (n <= kSmallMax)
-      sort_pass<VALS, kSmallBits, kSmallNT, kSmallItems, true>(b, n, shift, db,
-                                                               ctl, st);
-    else if (n <= kMidMax)
-      sort_pass<VALS, kMidBits, kTileNT, kTileItems, false>(b, n, shift, db,
-                                                            ctl, st);
-    else if (n <= kBigMax)
-      sort_pass<VALS, kBigBits, kTileNT, kTileItems, false>(b, n, shift, db,
-                                                            ctl, st);
-    else
-      sort_pass<VALS, kHugeBits, kTileNT, kTileItems, false>(b, n, shift, db,
-                                                             ctl, st);
+    sort_pass<VALS, DB, NT, ITEMS, SUM>(b, n, shift, db, ctl, st);
     std::swap(b.kin, b.kout);
     std::swap(b.vin, b.vout);
     shift += db;
-    flip = !flip;
   }
-  return flip;
+  return passes % 2 != 0;
 }
 
 }  // namespace
 
+// Pairs are sorted beyond the sizes whose values fit in the keys only.
 bool radix_sort_pairs(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt,
                       uint32_t *vals_alt, int32_t n, int nbits,
                       int32_t *hist, int32_t *bsum, int32_t *total, Ctl *ctl,
                       hipStream_t st) {
-  return sort_run<true>(
+  return sort_passes<true, kHugeBits, kTileNT, kTileItems, false>(
       SortBufs{keys, keys_alt, vals, vals_alt, hist, bsum, total}, n, 0, nbits,
       ctl, st);
 }
@@ -297,9 +283,18 @@ bool radix_sort_pairs(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt,
 bool radix_sort_keys(uint64_t *keys, uint64_t *keys_alt, int32_t n,
                      int shift0, int nbits, int32_t *hist, int32_t *bsum,
                      int32_t *total, Ctl *ctl, hipStream_t st) {
-  return sort_run<false>(
-      SortBufs{keys, keys_alt, nullptr, nullptr, hist, bsum, total}, n, shift0,
-      nbits, ctl, st);
+  const SortBufs b{keys, keys_alt, nullptr, nullptr, hist, bsum, total};
+  if (n <= kSmallMax)
+    return sort_passes<false, kSmallBits, kSmallNT, kSmallItems, true>(
+        b, n, shift0, nbits, ctl, st);
+  if (n <= kMidMax)
+    return sort_passes<false, kMidBits, kTileNT, kTileItems, false>(
+        b, n, shift0, nbits, ctl, st);
+  if (n <= kBigMax)
+    return sort_passes<false, kBigBits, kTileNT, kTileItems, false>(
+        b, n, shift0, nbits, ctl, st);
+  return sort_passes<false, kHugeBits, kTileNT, kTileItems, false>(
+      b, n, shift0, nbits, ctl, st);
 }
 
 // ---------------------------------------------------------------------------
