@@ -63,8 +63,17 @@ def test_hub_rows(hub, noise, tail_mode):
 def test_giant_components(sizes, tail_mode):
     # components that absorb `sizes` points in one round: a block each, shared
     # by blocks, ragged last segments; then merges among and into them
+    check_giants(sizes, 16)
+
+
+@pytest.mark.parametrize("d", [8, 32, 13, 64])
+def test_giant_components_by_width(d, tail_mode):
+    # shared by blocks (8, 32), and by one block (any other width)
+    check_giants((5000, 5121, 300), d)
+
+
+def check_giants(sizes, d):
     rng = np.random.default_rng(sum(sizes))
-    d = 16
     n = sum(sizes) + 3000
     nbr = np.full((n, 3), -1, np.int32)
     emb = (rng.standard_normal((n, d)) * 3).astype(np.float32)

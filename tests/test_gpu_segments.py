@@ -59,6 +59,28 @@ def test_segments(n, nc, d):
                             (kind, off, x is None, name)
 
 
+@pytest.mark.parametrize("n", [1_100_003, 3_000_001])
+@pytest.mark.parametrize("d", [16, 32, 64])
+def test_long_segments(n, d):
+    # up to 64 entries a group of lanes: several steps of a group, runs that
+    # end within a step and runs carried across steps, groups and blocks
+    if n * d > 10 ** 8:
+        pytest.skip("a smaller input covers this width's largest segments")
+    rng = np.random.default_rng(n + d)
+    lab = np.repeat(np.arange(n // 40, dtype=np.int32),
+                    rng.integers(1, 201, n // 40))[:n]
+    assert lab.size == n
+    lab = lab[rng.permutation(n)]
+    nc = int(lab.max()) + 1
+    emb = rng.standard_normal((n, d), dtype=np.float32)
+    xyz = rng.random((n, 3), dtype=np.float32) * 100
+    got = ezsp.component_stats(*(torch.from_numpy(lab).cuda(), nc,
+                                 torch.from_numpy(emb).cuda(),
+                                 torch.from_numpy(xyz).cuda()))
+    for a, b in zip(got, oracle.component_stats(lab, nc, emb, xyz)):
+        assert np.array_equal(a.cpu().numpy(), b)
+
+
 def test_segments_non_finite_and_range():
     lab = torch.zeros(1000, dtype=torch.int32, device="cuda")
     for value, code in ((float("nan"), ezsp.ERR_NONFINITE),
