@@ -304,7 +304,7 @@ int ezsp_embed_mlp(const uint16_t *x, int64_t n, int32_t d_in, int32_t d_hid,
  * outputs); stream-asynchronous, device-detected errors through
  * ezsp_sync_status(NULL, 0, stream).  The call allocates nothing: no
  * hipMalloc, hipFree or other allocating routine.  Sizes whose
- * ezsp_knn_workspace_size(n, k) exceeds 160 MiB (about 1.5M points at
+ * ezsp_knn_workspace_size(n, k) exceeds 160 MiB (about 1.69M points at
  * k = 10) return EZSP_ERR_INVALID_ARG.  Each GPU the library runs on holds
  * its own copy of the array until the process ends; every call on one GPU
  * uses that copy, so calls that overlap on one GPU (other streams, other

@@ -1147,8 +1147,8 @@ __global__ void k_jump_state(Ctl *ctl, int done) {
   }
 }
 
-// Roots numbered in node order; the pass also clears the member counters
-// of the next components (c < n_next <= nn).
+// Roots numbered in node order; the pass also starts the member counters
+// of the next components (c < n_next <= nn) at one, the root.
 struct ScanRoots {
   const int32_t *parent;
   int32_t *newid;
@@ -1203,9 +1203,10 @@ struct ScanWindows {
 // Component of every node and its place among the component's members.
 // The root is the first member, without an atomic: most nodes are roots
 // (a 10M-point terrain, whose rounds merge 2 to 6 % of the nodes: 37 -> 18 us
-// a call on average over the ladder).  Other nodes of one component mostly sit together in node order, so the lanes of a wave are
-// grouped by component (ballot per distinct value) and each group takes its
-// places with one atomic, made by its lowest lane.
+// a call on average over the ladder).  Other nodes of one component mostly
+// sit together in node order, so the lanes of a wave are grouped by component
+// (ballot per distinct value) and each group takes its places with one
+// atomic, made by its lowest lane.
 __global__ __launch_bounds__(256) void k_assign(int32_t nn,
                                                 const int32_t *parent,
                                                 const int32_t *newid,
@@ -1527,9 +1528,6 @@ __global__ __launch_bounds__(256) void k_stats_s(
   }
 }
 
-// k_stats_big for D = DT: one pass over the members, each thread summing
-// whole rows (16-byte loads, two members in flight), then a block
-// reduction (exact int64, so the order does not matter).
 // Partial sums of a giant component, joined by the blocks that share it:
 // the dimensions, then size, summed degree, INT32_MAX - smallest point, and
 // the segments done.  All zero between uses.
@@ -1538,6 +1536,9 @@ constexpr int32_t kGiantSeg = 1024;     // members a block takes at a time
 constexpr int32_t kGiantSlots = 4096;   // of the list of big components
 constexpr int32_t kGiantStride = 64 + 4;
 
+// k_stats_big for D = DT: one pass over the members, each thread summing
+// whole rows (16-byte loads, two members in flight), then a block
+// reduction (exact int64, so the order does not matter).
 // A block per component of more than big_members members; the blocks share
 // each of more than kGiantMembers, segment by segment, and the block that
 // ends the last segment writes the component.  (A giant component alone on
@@ -1727,6 +1728,8 @@ __global__ __launch_bounds__(256) void k_stats_big_t(
   }
 }
 
+// For any D: a block per component of more than big_members members, also
+// where it has hundreds of thousands.
 template <bool FIRST>
 __global__ __launch_bounds__(256) void k_stats_big(
     const int32_t *__restrict__ mem, const int32_t *__restrict__ moff,
@@ -2585,8 +2588,7 @@ struct TailState {
   int64_t *S;                              // sums, updated in place
   double *mu;                              // means, updated in place
   double *gain;                            // per listed edge
-  uint64_t *elist;                         // edges to evaluate:
-                                           // (v | u << 16) << 32 | w
+  uint64_t *elist;                         // edges to evaluate (tail_entry)
   int32_t *lvl_map, *lvl_minpt, *lvl_nc;  // kTailLevels x nn0 (nc: levels)
   int32_t *lvl_rank;                       // kTailLevels x nn0
   double *lvl_mu;                          // kTailLevels x nn0 x d
@@ -4547,7 +4549,6 @@ inline dim3 blocks_for(int64_t n, int nt = 256) {
   if (b < 1) b = 1;
   return dim3((unsigned)b);
 }
-constexpr int32_t kMapSync = 1 << 21;  // node maps worth bringing up to date
 
 inline dim3 xblocks_for(int64_t n) { return dim3(xcd_grid(blocks_for(n).x)); }
 
@@ -4989,8 +4990,6 @@ int incr_compact(const Bufs &b, Adj &adj, int &cur, int32_t n, int32_t &nn,
   return 0;
 }
 
-// The rest of the ladder in the tail kernel, then the labels (and energy)
-// of every level it ended.
 // The levels' energies from the control block read last: fidelity plus
 // lambda times the cut, cut0[l] / 2 where that is not negative (twice the
 // edges of the input graph, for a level without a merge).
@@ -5004,8 +5003,10 @@ void fill_energy(const LadderArgs &g, const Ctl *h, const int64_t *cut0) {
   }
 }
 
+// The rest of the ladder in the tail kernel, then the labels (and energy)
+// of every level it ended.
 int run_tail(const LadderArgs &g, const Bufs &b, const float *emb,
-             const int64_t *cut0, const Adj &adj, int cur, int32_t nn, int32_t ed, int32_t level0,
+             const int64_t *cut0, int cur, int32_t nn, int32_t level0,
              int32_t round0, int32_t max_rounds, Ctl *ctl, Ctl *h,
              hipStream_t st) {
   const int32_t n = g.n, d = g.d;
@@ -5062,7 +5063,6 @@ int run_tail(const LadderArgs &g, const Bufs &b, const float *emb,
     t.lambda[l] = l < g.n_levels ? g.lambdas[l] : 0.0;
     t.smin[l] = (l < g.n_levels && g.min_size) ? g.min_size[l] : 0;
   }
-  (void)adj;
   prof_begin("tail", st);
   switch (d) {
     case 8:
@@ -5454,8 +5454,10 @@ int ladder_run(const LadderArgs &g, Ctl *ctl, Arena &a, hipStream_t st) {
       const int32_t nn_before = nn;
       if (!first && mn == 0) mn = nn;  // the node map now spans this graph
       // a map of many more nodes than are left is composed through all of
-      // them every round (25 us at 9.7M): into the point map once, and the
-      // next rounds compose a small one
+      // them every round: into the point map once, and the next rounds
+      // compose a small one.  Measured at 9.7M nodes only (25 us a round); the
+      // bound is where that, in proportion, is a launch's worth.
+      constexpr int32_t kMapSync = 1 << 21;
       if (mn >= kMapSync && h->n_next < mn / 8) sync_map(b, n, mn, ctl, st);
       cur = 1 - cur;
       first = false;
@@ -5519,7 +5521,7 @@ int ladder_run(const LadderArgs &g, Ctl *ctl, Arena &a, hipStream_t st) {
   }
   if (tail_level >= 0) {
     // the tail's own readback comes after its last kernel
-    return run_tail(g, b, emb, cut0, adj, cur, nn, ed, tail_level, tail_round,
+    return run_tail(g, b, emb, cut0, cur, nn, tail_level, tail_round,
                     max_rounds, ctl, h, st);
   }
   if ((rc = read_ctl(ctl, h, st))) return rc;
