@@ -32,7 +32,8 @@
 //   k_le_sample  the intra pairs below that bin: loss and gradient; those in
 //                it are listed
 //   k_le_select  the threshold among the listed keys
-//   k_le_listed  the listed pairs up to the threshold
+//   k_le_pairs   (DRAWN) the listed pairs up to the threshold
+//   k_le_total   the partial losses added up
 // The embedding rows and the neighbours' table rows are gathered once; a
 // small sample's rows are gathered again.  Where the guess says that the
 // sample is a large part of the pairs, k_le_pairs only classifies, k_le_sample
